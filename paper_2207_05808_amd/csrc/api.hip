@@ -935,7 +935,7 @@ int maddness_build_lut(const float* P, const float* B, int32_t C, int32_t D, int
   if (C > kMaxC) return MADDNESS_EUNSUPPORTED;
   int cap = 0;
   while (127.0 * C * (double)(1ll << (cap + 1)) < 16777216.0) ++cap;
-  return status_from(launch_build_lut(P, B, C, D, M, lut_out, scale_out, offset_out, cap,
+  return status_from(launch_build_lut(P, B, C, D, M, lut_out, scale_out, offset_out, cap, device_cus(),
                                       static_cast<hipStream_t>(stream)));
 }
 
@@ -946,7 +946,7 @@ int maddness_build_lut_shared(const float* P, const float* B, int32_t C, int32_t
   if (!aligned(P, 4) || !aligned(B, 4) || !aligned(scale_out, 4) || !aligned(offset_out, 4))
     return MADDNESS_EINVAL;
   if (C > kMaxC) return MADDNESS_EUNSUPPORTED;
-  return status_from(launch_build_lut(P, B, C, D, M, lut_out, scale_out, offset_out, 0,
+  return status_from(launch_build_lut(P, B, C, D, M, lut_out, scale_out, offset_out, 0, device_cus(),
                                       static_cast<hipStream_t>(stream)));
 }
 
@@ -1053,7 +1053,7 @@ int maddness_build_lut_f32(const float* P, const float* B, int32_t C, int32_t D,
   if (C <= 0 || D <= 0 || M <= 0 || !P || !B || !lut_out) return MADDNESS_EINVAL;
   if (!aligned(P, 4) || !aligned(B, 4) || !aligned(lut_out, 4)) return MADDNESS_EINVAL;
   if (C > kMaxC) return MADDNESS_EUNSUPPORTED;
-  return status_from(launch_build_lut_f32(P, B, C, D, M, lut_out, static_cast<hipStream_t>(stream)));
+  return status_from(launch_build_lut_f32(P, B, C, D, M, lut_out, device_cus(), static_cast<hipStream_t>(stream)));
 }
 
 }  // extern "C"

@@ -215,9 +215,9 @@ hipError_t launch_path(int mode, int elem, int pf, int uq, const KArgs& a,
 // Offline table build (T = P B, quantization); see lut_build.hip.
 hipError_t launch_build_lut(const float* P, const float* B, int C, int D, int M,
                             int8_t* lut, float* scale, float* offset, int cap,
-                            hipStream_t stream);
+                            int cus, hipStream_t stream);
 hipError_t launch_build_lut_f32(const float* P, const float* B, int C, int D, int M,
-                                float* lut, hipStream_t stream);
+                                float* lut, int cus, hipStream_t stream);
 hipError_t launch_quantize_lut(const double* T, int C, int M, int8_t* lut, float* scale, float* offset,
                                int cap, hipStream_t stream);
 
