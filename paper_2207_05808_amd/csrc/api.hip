@@ -1040,11 +1040,10 @@ int maddness_fit_lut_gd(const uint8_t* idx, int64_t N, int32_t C, const float* Y
   w += round_up64(N * M * 8, 256);
   double* D = reinterpret_cast<double*>(w);
   w += round_up64(N * M * 8, 256);
-  double* R = reinterpret_cast<double*>(w);
-  w += round_up64((int64_t)C * kK * M * 8, 256);
+  w += round_up64((int64_t)C * kK * M * 8, 256);   // (unused: the gradient is not stored)
   int32_t* perm = reinterpret_cast<int32_t*>(w);
   int32_t* start = reinterpret_cast<int32_t*>(w + round_up64((int64_t)C * (N + 128) * 4, 256));
-  return status_from(launch_fit_gd(idx, N, C, Y, M, col_bias, act, T0, lambda, eta, iters, T_out, P, D, R, perm,
+  return status_from(launch_fit_gd(idx, N, C, Y, M, col_bias, act, T0, lambda, eta, iters, T_out, P, D, perm,
                                    start, static_cast<hipStream_t>(stream)));
 }
 

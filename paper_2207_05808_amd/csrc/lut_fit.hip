@@ -14,9 +14,9 @@
 //           atomics: the result does not depend on their order).
 //   scatter R = G^T Y in double: a stable counting sort lists each
 //           codebook's rows bucket by bucket (ascending within a bucket),
-//           then one wavefront per (codebook, 64 columns), lane = column,
-//           sums each bucket's rows in that order: every entry is the sum of
-//           its rows in ascending row order.
+//           then one workgroup per (codebook, bucket, 64 columns)
+//           sums the bucket's rows in that order: every entry is the
+//           sum of its rows in ascending row order.
 //   solve   A = H + lambda I (double), B = R + lambda T0; A = L L^T by a
 //           blocked right-looking Cholesky factorisation (panels of 32:
 //           diagonal block in one workgroup, the rows below it, then the
@@ -80,115 +80,290 @@ gram_kernel(const uint8_t* __restrict__ idx, int64_t N, int C, int nbc, int64_t 
 // --------------------------------------------------------------- scatter
 // R[16c + k][m] = sum over rows n (ascending) with idx[n][c] = k of Y[n][m].
 //
-// partition: one wavefront per codebook lists the rows bucket by bucket,
-// ascending within each bucket (a stable counting sort: per 64-row batch, one
-// ballot per bucket gives each row its rank among the batch's rows of its
-// bucket), perm[c][start_k ..] = rows of bucket k, start[c][k] the bucket
-// starts (start[c][16] = N).  Each codebook's list is followed by 128 entries
-// of row 0, read (and ignored) by the last two batches of the scatter.
+// partition: one workgroup per codebook lists the rows bucket by bucket,
+// ascending within each bucket (a stable counting sort), perm[c][start_k ..] =
+// rows of bucket k, start[c][k] the bucket starts (start[c][16] = N).  Each
+// codebook's list is followed by 128 entries of row 0, read (and ignored) past the last
+// bucket.
 constexpr int kPermPad = 128;
 
-__global__ void __launch_bounds__(64)
+constexpr int kPartWaves = 16;
+
+// One workgroup per codebook; wavefront w takes the w-th contiguous run of
+// whole 64-row batches, counts its buckets, and after one barrier knows where
+// its rows of each bucket go (bucket-major, then wavefront: stable).  The
+// rank of a row among its batch's rows of the same bucket comes from 4 ballots
+// (one per index bit).  Bound: load latency, 8 batches requested together
+// (16,384 rows x 64 codebooks: 312 -> 23 us against one
+// wavefront per codebook).
+__global__ void __launch_bounds__(kPartWaves * 64)
 partition_kernel(const uint8_t* __restrict__ idx, int64_t N, int C, int32_t* __restrict__ perm,
                  int32_t* __restrict__ start) {
-  const int lane = threadIdx.x;
+  __shared__ int s_cnt[kPartWaves][kK];   // rows per bucket of a wavefront, then its next position
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = blockIdx.x;
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));   // lanes below this one
-  int64_t cnt[kK];
+  const uint64_t lt = (1ull << lane) - 1;   // lanes below this one
+  const int64_t batches = (N + 63) / 64;
+  const int64_t b0 = batches * wave / kPartWaves, b1 = batches * (wave + 1) / kPartWaves;
+  constexpr int kU = 8;
+  auto load = [&](int64_t b, int (&key)[kU]) {
 #pragma unroll
-  for (int k = 0; k < kK; ++k) cnt[k] = 0;
-  for (int64_t n0 = 0; n0 < N; n0 += 64) {
-    const int key = (n0 + lane < N) ? (int)(idx[(n0 + lane) * C + c] & 15) : kK;
+    for (int u = 0; u < kU; ++u) {
+      const int64_t n = (b + u) * 64 + lane;
+      key[u] = b + u < b1 && n < N ? (int)(idx[n * C + c] & 15) : kK;
+    }
+  };
+  // lanes of this batch whose row is in the same bucket (key < 16)
+  auto same = [&](int key) {
+    uint64_t m = __ballot(key < kK);
 #pragma unroll
-    for (int k = 0; k < kK; ++k) cnt[k] += __popcll(__ballot(key == k));
+    for (int bit = 0; bit < 4; ++bit) {
+      const uint64_t v = __ballot((key >> bit) & 1);
+      m &= (key >> bit) & 1 ? v : ~v;
+    }
+    return m;
+  };
+  // orders a wavefront's own LDS accesses across its lanes (no instruction)
+  auto in_order = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  if (lane < kK) s_cnt[wave][lane] = 0;
+  in_order();
+  for (int64_t b = b0; b < b1; b += kU) {
+    int key[kU];
+    load(b, key);
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const uint64_t m = same(key[u]);
+      if (key[u] < kK && (m & lt) == 0) s_cnt[wave][key[u]] += __popcll(m);
+      in_order();
+    }
   }
-  int64_t pos[kK];
-  int64_t run = 0;
-#pragma unroll
-  for (int k = 0; k < kK; ++k) {
-    pos[k] = run;
-    if (lane == 0) start[c * (kK + 1) + k] = (int32_t)run;
-    run += cnt[k];
+  __syncthreads();
+  if (threadIdx.x < kK) {   // lane k: the bucket's rows in all, the buckets before it, then its wavefronts
+    int total = 0;
+    for (int w = 0; w < kPartWaves; ++w) total += s_cnt[w][lane];
+    int run = total;
+    for (int o = 1; o < kK; o <<= 1) {
+      const int v = __shfl_up(run, o);
+      if (lane >= o) run += v;
+    }
+    run -= total;
+    start[c * (kK + 1) + lane] = run;
+    for (int w = 0; w < kPartWaves; ++w) {
+      const int v = s_cnt[w][lane];
+      s_cnt[w][lane] = run;
+      run += v;
+    }
   }
-  if (lane == 0) start[c * (kK + 1) + kK] = (int32_t)N;
+  if (threadIdx.x == 0) start[c * (kK + 1) + kK] = (int32_t)N;
+  __syncthreads();
   int32_t* pc = perm + (int64_t)c * (N + kPermPad);
-  pc[N + lane] = 0;
-  pc[N + 64 + lane] = 0;
-  for (int64_t n0 = 0; n0 < N; n0 += 64) {
-    const int key = (n0 + lane < N) ? (int)(idx[(n0 + lane) * C + c] & 15) : kK;
+  if (threadIdx.x < kPermPad) pc[N + threadIdx.x] = 0;
+  for (int64_t b = b0; b < b1; b += kU) {
+    int key[kU];
+    load(b, key);
 #pragma unroll
-    for (int k = 0; k < kK; ++k) {
-      const uint64_t mask = __ballot(key == k);
-      if (key == k) pc[pos[k] + __popcll(mask & lt)] = (int32_t)(n0 + lane);
-      pos[k] += __popcll(mask);
+    for (int u = 0; u < kU; ++u) {
+      const uint64_t m = same(key[u]);
+      const int at = s_cnt[wave][key[u] & 15];
+      in_order();
+      if (key[u] < kK) {
+        pc[at + __popcll(m & lt)] = (int32_t)((b + u) * 64 + lane);
+        if ((m & lt) == 0) s_cnt[wave][key[u]] = at + __popcll(m);
+      }
+      in_order();
     }
   }
 }
 
-// scatter: one wavefront per (codebook, 64-column tile), lane = column.  The
-// codebook's row list is walked in batches of kSR positions (64 for float
-// inputs, 32 for double; the next batch's loads in flight while the current
-// one is added); a running double
-// sum takes the rows in list order and is stored and restarted at each
-// bucket end, so every entry is its bucket's rows summed in ascending order.
-// V: float (targets Y) or double (gradient residuals); kSR positions per batch
-template <class V, int kSR>
-__global__ void __launch_bounds__(64)
-scatter_kernel(const int32_t* __restrict__ perm, const int32_t* __restrict__ start, int64_t N, int C,
-               const V* __restrict__ Y, int M, double* __restrict__ R) {
-  __shared__ V s_v[kSR][64];
-  const int lane = threadIdx.x;
-  const int ntile = (M + 63) / 64;
-  const int c = blockIdx.x / ntile;
-  const int m = (blockIdx.x % ntile) * 64 + lane;
-  const bool ok = m < M;
-  const V* yc = Y + min(m, M - 1);
-  const int32_t* pc = perm + (int64_t)c * (N + kPermPad);
-  const int32_t* sc = start + c * (kK + 1);
-  double* rc = R + (int64_t)c * kK * M + m;
-  int k = 0;
-  int64_t end = sc[1];   // end of bucket k
-  double acc = 0.0;
-  // store and restart the sums of every bucket that ends at position p
-  auto close_buckets = [&](int64_t p) {
-    while (k < kK && end == p) {
-      if (ok) rc[(int64_t)k * M] = acc;
-      acc = 0.0;
-      ++k;
-      end = (k < kK) ? sc[k + 1] : -1;
-    }
-  };
-  // positions past N read the padding (row 0) and columns past M column
-  // M - 1: every load is valid, unused values are ignored; the row numbers
-  // are uniform (scalar loads)
-  V v[kSR], vn[kSR];
-  if (N > 0) {
-#pragma unroll
-    for (int j = 0; j < kSR; ++j) v[j] = yc[(int64_t)pc[j] * M];
+// scatter: one workgroup per (codebook, bucket, TC columns) walks the bucket's
+// rows in stages.  Seven wavefronts load them (8 rows per lane and stage,
+// 64 / TC row groups side by side, some stages ahead in registers) and hand
+// them over through LDS, 16 bytes per lane and access (2 rows of doubles or 4
+// of floats of one column together); the first wavefront, lane = column, adds
+// them: every entry is its bucket's rows summed in ascending order.  V: float
+// (targets Y) or double (gradient residuals).  `done(bucket row, column, sum)`
+// takes the result: stores it, or takes the gradient step.
+//
+// The sum of a bucket is one chain of dependent adds (4.5 cycles each), and
+// buckets are uneven (the largest of a random tree's 16 holds about half of
+// the rows), so the adding wavefront does nothing else.  Bound: on small
+// layers that chain, on large ones the L2, which reads every row once per
+// codebook.  Column tiles go to XCDs (workgroup b runs on XCD b % 8): with a
+// number of tiles that divides 8, or a multiple of 8, each XCD reads its own
+// columns only, and TC is such that they fit its 4 MB L2 at the training sets'
+// sizes; else the tiles are taken one after the other.
+// Measured against one wavefront per codebook with its 16 buckets in turn:
+// 16,384 rows, 32 codebooks x 64 columns of doubles 554 -> 79 us (largest
+// bucket 9063 rows); 64 codebooks x 512 columns of floats 585 -> 163 us (2.1 GB
+// out of the L2s).
+constexpr int kScWaves = 8, kScPer = 8;   // wavefronts; rows of a loading lane per stage
+
+// a barrier that orders LDS only: global loads stay in flight across it
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <class V, int TC, class F>
+__device__ __forceinline__ void scatter_bucket(const int32_t* __restrict__ perm, const int32_t* __restrict__ start,
+                                               int64_t N, int C, const V* __restrict__ Y, int M, F&& done) {
+  constexpr int R = 16 / (int)sizeof(V);              // rows of one LDS access
+  typedef V Pack __attribute__((ext_vector_type(R)));
+  constexpr int kPer = kScPer * (64 / TC);            // rows of a loading wavefront per stage
+  constexpr int kRows = (kScWaves - 1) * kPer;        // rows of a stage
+  constexpr int kPacks = kRows / R;
+  constexpr int kDepth = 64 / kPer < 4 ? 64 / kPer : 4;   // stages in flight; at most one row number per lane
+  constexpr int kAhead = 7;                           // LDS reads ahead of the adds
+  static_assert(kPacks % kAhead == 0, "whole chunks");
+  __shared__ Pack s_row[2][kPacks][TC];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ntile = (M + TC - 1) / TC, rows = C * kK;
+  int tile, r;
+  if (ntile % 8 == 0) {
+    const int j = blockIdx.x >> 3;
+    tile = (blockIdx.x & 7) + 8 * (j / rows);
+    r = j % rows;
+  } else if (8 % ntile == 0) {
+    tile = blockIdx.x % ntile;
+    r = blockIdx.x / ntile;
+  } else {
+    tile = blockIdx.x / rows;
+    r = blockIdx.x % rows;
   }
-  for (int64_t p0 = 0; p0 < N; p0 += kSR) {
-    const int32_t* pn = pc + p0 + kSR;
+  // every codebook's largest bucket first, then the second largest, ...: the
+  // long chains start at once
+  const int c = r % C;
+  int k;
+  {
+    const int32_t* sc = start + c * (kK + 1);
+    const int size = lane < kK ? sc[lane + 1] - sc[lane] : -1;
+    int rank = 0;
 #pragma unroll
-    for (int j = 0; j < kSR; ++j) vn[j] = yc[(int64_t)pn[j] * M];
-    if (end >= p0 + kSR) {
-      // the whole batch lies in bucket k
+    for (int j = 0; j < kK; ++j) {
+      const int o = __builtin_amdgcn_readlane(size, j);
+      rank += o > size || (o == size && j < lane);
+    }
+    k = __ffsll(__ballot(lane < kK && rank == r / C)) - 1;
+  }
+  const int m = tile * TC + lane % TC;
+  const int64_t p0 = start[c * (kK + 1) + k], p1 = start[c * (kK + 1) + k + 1];
+  // whole groups of kDepth stages (the last ones may have no rows): no branch
+  // in the loaders' loop, where the compiler would wait for every load in
+  // flight at the join
+  const int64_t nst = (p1 - p0 + kRows * kDepth - 1) / (kRows * kDepth) * kDepth;
+  if (wave != 0) {
+    // a lane holds one row number of the next kDepth stages (row lane % kPer
+    // of stage lane / kPer), read a group of stages ahead; rows past the
+    // bucket are its last one, columns past M column M - 1: every load is
+    // valid, what is not used is ignored
+    if (nst == 0) return;
+    const V* yc = Y + min(m, M - 1);
+    const int32_t* pc = perm + (int64_t)c * (N + kPermPad);
+    const int64_t mine = p0 + lane / kPer % kDepth * kRows + (wave - 1) * kPer + lane % kPer;
+    const int first = lane / TC * kScPer;   // this lane's first row of the wavefront's
+    auto fetch = [&](int64_t st) { return pc[min(mine + st * kRows, p1 - 1)]; };
+    V v[kDepth][kScPer];
+    auto load = [&](int d, int numbers, V (&to)[kScPer]) {
 #pragma unroll
-      for (int j = 0; j < kSR; ++j) acc = __dadd_rn(acc, (double)v[j]);
-    } else {
-      // a bucket ends inside the batch (at most 16 + 1 batches): position by
-      // position, the values parked in LDS (this lane's own column)
+      for (int j = 0; j < kScPer; ++j) {
+        const int n = TC == 64 ? __builtin_amdgcn_readlane(numbers, d * kPer + j)
+                               : __shfl(numbers, d * kPer + first + j);
+        to[j] = yc[(int64_t)n * M];
+      }
+    };
+    auto put = [&](int64_t st, const V (&from)[kScPer]) {
 #pragma unroll
-      for (int j = 0; j < kSR; ++j) s_v[j][lane] = v[j];
-#pragma unroll 1
-      for (int j = 0; j < kSR; ++j) {
-        close_buckets(p0 + j);
-        if (p0 + j < N) acc = __dadd_rn(acc, (double)s_v[j][lane]);
+      for (int j = 0; j < kScPer; j += R) {
+        Pack q;
+#pragma unroll
+        for (int i = 0; i < R; ++i) q[i] = from[j + i];
+        s_row[st & 1][((wave - 1) * kPer + first + j) / R][lane % TC] = q;
+      }
+    };
+    int now = fetch(0), next = fetch(kDepth);
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d) load(d, now, v[d]);
+    put(0, v[0]);
+    lds_barrier();
+    for (int64_t st = 0; st < nst; st += kDepth) {
+      now = next;
+      next = fetch(st + 2 * kDepth);
+#pragma unroll
+      for (int d = 0; d < kDepth; ++d) {   // stage st + d + 1 to LDS, st + d + kDepth requested
+        load(d, now, v[d]);
+        put(st + d + 1, v[(d + 1) % kDepth]);
+        lds_barrier();
       }
     }
-#pragma unroll
-    for (int j = 0; j < kSR; ++j) v[j] = vn[j];
+    return;
   }
-  close_buckets(N);
+  double acc = 0.0;
+  __builtin_amdgcn_s_setprio(3);
+  if (nst > 0) lds_barrier();
+  for (int64_t st = 0; st < nst; ++st) {
+    const Pack(&row)[kPacks][TC] = s_row[st & 1];
+    const int64_t left = p1 - p0 - st * kRows;
+    // chunks of kAhead packs: the next chunk's reads go out between this one's
+    // adds (scheduling barriers: left alone the compiler reads two rows ahead,
+    // and reads in groups hold up the adds behind them).  Kept a short loop:
+    // unrolled over the stage, most of the time went into fetching its code.
+    const int n = (int)(left < kRows ? (left > 0 ? left : 0) : kRows);
+    Pack g[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) g[i] = row[i][lane % TC];
+    int at = 0;   // first pack of the chunk
+#pragma unroll 1
+    for (; (at + kAhead) * R <= n; at += kAhead) {
+      const int next = at + kAhead < kPacks ? at + kAhead : 0;
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) acc = __dadd_rn(acc, (double)g[i][j]);
+        g[i] = row[next + i][lane % TC];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    // the bucket's last rows; those past it add +0: the sum starts at +0 and
+    // is never -0
+    if (at * R < n) {
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+        for (int j = 0; j < R; ++j) acc = __dadd_rn(acc, (at + i) * R + j < n ? (double)g[i][j] : 0.0);
+    }
+    lds_barrier();
+  }
+  if (lane < TC && m < M) done((int64_t)c * kK + k, m, acc);
+}
+
+constexpr int kScCols = 64;                                            // columns of floats per workgroup
+constexpr int step_cols(int M) { return M <= 128 ? 16 : 32; }          // of doubles: 8 tiles, or the fewer LDS accesses
+unsigned scatter_grid(int C, int M, int cols) { return (unsigned)(C * kK * ((M + cols - 1) / cols)); }
+
+__global__ void __launch_bounds__(kScWaves * 64)
+scatter_kernel(const int32_t* __restrict__ perm, const int32_t* __restrict__ start, int64_t N, int C,
+               const float* __restrict__ Y, int M, double* __restrict__ R) {
+  scatter_bucket<float, kScCols>(perm, start, N, C, Y, M, [&](int64_t r, int m, double v) { R[r * M + m] = v; });
+}
+
+// The gradient step on the sums just made: T = T - eta (R + 2 lambda (T - T0))
+template <int TC>
+__global__ void __launch_bounds__(kScWaves * 64)
+scatter_step_kernel(const int32_t* __restrict__ perm, const int32_t* __restrict__ start, int64_t N, int C,
+                    const double* __restrict__ Dv, int M, const float* __restrict__ T0, double lam, double eta,
+                    double* __restrict__ T) {
+  const double two_lam = __dmul_rn(2.0, lam);
+  scatter_bucket<double, TC>(perm, start, N, C, Dv, M, [&](int64_t r, int m, double v) {
+    const int64_t e = r * M + m;
+    const double g = __dadd_rn(v, __dmul_rn(two_lam, __dsub_rn(T[e], (double)T0[e])));
+    T[e] = __dsub_rn(T[e], __dmul_rn(eta, g));
+  });
 }
 
 // -------------------------------------------------------------- assemble
@@ -426,22 +601,114 @@ target_kernel(const float* __restrict__ Y, int64_t N, int M, const float* __rest
   }
 }
 
+// The sums over the codebooks, c ascending, of row n's table rows at columns
+// lane, lane + 64, ... (J of them; columns past M read column M - 1): the
+// indices come 64 codebooks at a time, one per lane, and are handed out
+// through readlane, so a table row's address is uniform and 8 codebooks' loads
+// are in flight.  n is uniform.
+template <int J>
+__device__ __forceinline__ void gather_row(const uint8_t* __restrict__ ir, int C, const double* __restrict__ T, int M,
+                                           int m0, int lane, double (&s)[J]) {
+  int col[J];
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    s[j] = 0.0;
+    col[j] = min(m0 + lane + 64 * j, M - 1);
+  }
+  for (int c0 = 0; c0 < C; c0 += 64) {
+    const int key = c0 + lane < C ? (int)(ir[c0 + lane] & 15) : 0;
+    const double* tc = T + (int64_t)c0 * kK * M;
+    const int nc = min(64, C - c0);
+    constexpr int kU = 8;
+    for (int c = 0; c < nc; c += kU) {
+      double v[kU][J];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int cu = min(c + u, nc - 1);
+        const double* row = tc + (int64_t)(cu * kK + __builtin_amdgcn_readlane(key, cu)) * M;
+#pragma unroll
+        for (int j = 0; j < J; ++j) v[u][j] = row[col[j]];
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u)
+        if (c + u < nc) {
+#pragma unroll
+          for (int j = 0; j < J; ++j) s[j] = __dadd_rn(s[j], v[u][j]);
+        }
+    }
+  }
+}
+
 // D = dObjective / dz per row: ReLU 2 (relu(z) - P) [z > 0]; softmax with the
 // KL divergence softmax(z) - P; softmax with the squared error 2 p (d - s),
 // p = softmax(z), d = p - P, s = sum_m d_m p_m (the softmax Jacobian
-// diag(p) - p p^T applied to 2 d).
+// diag(p) - p p^T applied to 2 d).  One wavefront per row; rows of at most
+// 64 J columns stay in registers, each lane's columns in the same order as
+// through memory.  Bound: the table rows out of the L2, 8 bytes per (row,
+// codebook, column) (16,384 x 32 x 64: 44 -> 26 us, 10 TB/s).
+template <int J>
+__global__ void __launch_bounds__(256)
+resid_reg_kernel(const uint8_t* __restrict__ idx, int64_t N, int C, const double* __restrict__ T, int M,
+                 const float* __restrict__ bias, int act, const double* __restrict__ P, double* __restrict__ D) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int64_t n = (int64_t)blockIdx.x * 4 + wave; n < N; n += (int64_t)gridDim.x * 4) {
+    double z[J], p[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) p[j] = P[n * M + min(lane + 64 * j, M - 1)];
+    gather_row<J>(idx + n * C, C, T, M, 0, lane, z);
+#pragma unroll
+    for (int j = 0; j < J; ++j) z[j] = __dadd_rn(z[j], bias ? (double)bias[min(lane + 64 * j, M - 1)] : 0.0);
+    if (act == 2) {
+#pragma unroll
+      for (int j = 0; j < J; ++j) z[j] = z[j] > 0.0 ? __dmul_rn(2.0, __dsub_rn(z[j], p[j])) : 0.0;
+    } else {
+      double mx = -__builtin_inf(), sum = 0.0;
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+        if (lane + 64 * j < M) mx = fmax(mx, z[j]);
+      mx = wave_max(mx);
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+        if (lane + 64 * j < M) {
+          z[j] = exp(__dsub_rn(z[j], mx));
+          sum = __dadd_rn(sum, z[j]);
+        }
+      sum = wave_sum(sum);
+#pragma unroll
+      for (int j = 0; j < J; ++j) z[j] = __ddiv_rn(z[j], sum);
+      if (act == 3) {
+#pragma unroll
+        for (int j = 0; j < J; ++j) z[j] = __dsub_rn(z[j], p[j]);
+      } else {
+        double s = 0.0;
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+          if (lane + 64 * j < M) s = __dadd_rn(s, __dmul_rn(__dsub_rn(z[j], p[j]), z[j]));
+        s = wave_sum(s);
+#pragma unroll
+        for (int j = 0; j < J; ++j) z[j] = __dmul_rn(2.0, __dmul_rn(z[j], __dsub_rn(__dsub_rn(z[j], p[j]), s)));
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+      if (lane + 64 * j < M) D[n * M + lane + 64 * j] = z[j];
+  }
+}
+
+// the same for rows of any width: the row goes through D
 __global__ void __launch_bounds__(256)
 resid_kernel(const uint8_t* __restrict__ idx, int64_t N, int C, const double* __restrict__ T, int M,
              const float* __restrict__ bias, int act, const double* __restrict__ P, double* __restrict__ D) {
   const int lane = threadIdx.x & 63;
-  for (int64_t n = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); n < N; n += (int64_t)gridDim.x * 4) {
-    const uint8_t* ir = idx + n * C;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int64_t n = (int64_t)blockIdx.x * 4 + wave; n < N; n += (int64_t)gridDim.x * 4) {
     double* dr = D + n * M;
     const double* pr = P + n * M;
     for (int m = lane; m < M; m += 64) {
-      double s = 0.0;
-      for (int c = 0; c < C; ++c) s = __dadd_rn(s, T[((int64_t)c * kK + (ir[c] & 15)) * M + m]);
-      const double z = __dadd_rn(s, bias ? (double)bias[m] : 0.0);
+      double s[1];
+      gather_row<1>(idx + n * C, C, T, M, m - lane, lane, s);
+      const double z = __dadd_rn(s[0], bias ? (double)bias[m] : 0.0);
       dr[m] = (act == 2) ? (z > 0.0 ? __dmul_rn(2.0, __dsub_rn(z, pr[m])) : 0.0) : z;
     }
     if (act == 3) {
@@ -457,17 +724,6 @@ resid_kernel(const uint8_t* __restrict__ idx, int64_t N, int C, const double* __
         dr[m] = __dmul_rn(2.0, __dmul_rn(p, __dsub_rn(__dsub_rn(p, pr[m]), s)));
       }
     }
-  }
-}
-
-// T = T - eta (R + 2 lambda (T - T0))
-__global__ void __launch_bounds__(256)
-gd_update_kernel(double* __restrict__ T, const float* __restrict__ T0, const double* __restrict__ R, double lam,
-                 double eta, int64_t total) {
-  const double two_lam = __dmul_rn(2.0, lam);
-  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
-    const double g = __dadd_rn(R[e], __dmul_rn(two_lam, __dsub_rn(T[e], (double)T0[e])));
-    T[e] = __dsub_rn(T[e], __dmul_rn(eta, g));
   }
 }
 
@@ -507,16 +763,7 @@ hipError_t launch_gram(const uint8_t* idx, int64_t N, int C, int32_t* H, int cus
 
 hipError_t launch_partition(const uint8_t* idx, int64_t N, int C, int32_t* perm, int32_t* start,
                             hipStream_t stream) {
-  hipLaunchKernelGGL(partition_kernel, dim3((unsigned)C), dim3(64), 0, stream, idx, N, C, perm, start);
-  return hipGetLastError();
-}
-
-template <class V, int kSR>
-hipError_t launch_scatter_sorted(const int32_t* perm, const int32_t* start, int64_t N, int C, const V* Y, int M,
-                                 double* R, hipStream_t stream) {
-  const int ntile = (M + 63) / 64;
-  hipLaunchKernelGGL((scatter_kernel<V, kSR>), dim3((unsigned)(C * ntile)), dim3(64), 0, stream, perm, start, N, C,
-                     Y, M, R);
+  hipLaunchKernelGGL(partition_kernel, dim3((unsigned)C), dim3(kPartWaves * 64), 0, stream, idx, N, C, perm, start);
   return hipGetLastError();
 }
 
@@ -524,7 +771,9 @@ hipError_t launch_scatter(const uint8_t* idx, int64_t N, int C, const float* Y, 
                           int32_t* perm, int32_t* start, hipStream_t stream) {
   hipError_t e = launch_partition(idx, N, C, perm, start, stream);
   if (e != hipSuccess) return e;
-  return launch_scatter_sorted<float, 64>(perm, start, N, C, Y, M, R, stream);
+  hipLaunchKernelGGL(scatter_kernel, dim3(scatter_grid(C, M, kScCols)), dim3(kScWaves * 64), 0, stream, perm, start, N,
+                     C, Y, M, R);
+  return hipGetLastError();
 }
 
 hipError_t launch_fit_ridge(const uint8_t* idx, int64_t N, int C, const float* Y, int M, const float* T0,
@@ -575,7 +824,7 @@ hipError_t launch_fit_ridge(const uint8_t* idx, int64_t N, int C, const float* Y
 
 hipError_t launch_fit_gd(const uint8_t* idx, int64_t N, int C, const float* Y, int M, const float* bias, int act,
                          const float* T0, double lam, double eta, int iters, double* T, double* P, double* D,
-                         double* R, int32_t* perm, int32_t* start, hipStream_t stream) {
+                         int32_t* perm, int32_t* start, hipStream_t stream) {
   const int64_t total = (int64_t)C * kK * M;
   hipLaunchKernelGGL(copy_f32_f64_kernel, dim3(grid_1d(total, 256)), dim3(256), 0, stream, T0, T, total);
   hipError_t e = hipGetLastError();
@@ -588,11 +837,14 @@ hipError_t launch_fit_gd(const uint8_t* idx, int64_t N, int C, const float* Y, i
   }
   for (int it = 0; it < iters; ++it) {
     if (N > 0) {
-      hipLaunchKernelGGL(resid_kernel, dim3(rows), dim3(256), 0, stream, idx, N, C, T, M, bias, act, P, D);
+      auto resid = M <= 64 ? resid_reg_kernel<1> : M <= 128 ? resid_reg_kernel<2> : M <= 256 ? resid_reg_kernel<4>
+                                                                                             : resid_kernel;
+      hipLaunchKernelGGL(resid, dim3(rows), dim3(256), 0, stream, idx, N, C, T, M, bias, act, P, D);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if ((e = launch_scatter_sorted<double, 32>(perm, start, N, C, D, M, R, stream)) != hipSuccess) return e;
-    hipLaunchKernelGGL(gd_update_kernel, dim3(grid_1d(total, 256)), dim3(256), 0, stream, T, T0, R, lam, eta, total);
+    auto step = step_cols(M) == 16 ? scatter_step_kernel<16> : scatter_step_kernel<32>;
+    hipLaunchKernelGGL(step, dim3(scatter_grid(C, M, step_cols(M))), dim3(kScWaves * 64), 0, stream, perm,
+                       start, N, C, D, M, T0, lam, eta, T);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
