@@ -179,12 +179,14 @@ int maddness_lut_accumulate_f32(const uint8_t* idx, int64_t N, int32_t C,
  * output.  When the table [C][16][M] fits the single-launch kernels the
  * indices never leave the chip and idx_out is optional (written when given).
  * Otherwise the rows are encoded into idx_out and then accumulated, and
- * idx_out is required: EINVAL when it is NULL.  One case sits between: int8
- * tables of 64 codebooks and 16 <= M <= 512 columns at 98304 rows or more
- * run as one launch without idx_out, but given an 8-byte aligned idx_out
- * with M >= 128 they run faster in two phases through it (encode, then the
- * lookup-accumulate as a one-hot int8 product on the matrix cores, §2.2's
- * encoder output taken as a 0/1 matrix).  maddness_matmul_index_bytes tells
+ * idx_out is required: EINVAL when it is NULL.  Some calls sit between: they
+ * run as one launch without idx_out, but given an 8-byte aligned idx_out they
+ * run faster in two phases through it (encode, then the lookup-accumulate as a
+ * one-hot int8 product on the matrix cores, §2.2's encoder output taken as a
+ * 0/1 matrix).  Those are int8 tables with C % 16 == 0, C <= 128 and M % 4 == 0
+ * of 64 codebooks and 128 to 512 columns at 98304 rows or more, or with C * M
+ * >= 3072 where the table fits the LDS but not in 16-byte units of the
+ * gather-fused kernel.  maddness_matmul_index_bytes tells
  * which case a call is.
  */
 int maddness_matmul(const float* A, int64_t N, int32_t D, int64_t lda,

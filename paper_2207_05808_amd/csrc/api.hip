@@ -521,38 +521,53 @@ bool plan_tavg(const Shape& s, TArgs* t, int* nw_out) {
 }
 
 // One-hot product on the matrix cores (onehot_mfma.hip): int8 tables with
-// C % 16 == 0 and 48 <= C <= 128, M % 4 == 0 and M >= 128, a 4-byte aligned
-// table, 8-byte aligned index rows and 16-byte aligned outputs, at row counts
-// where each of the workgroups (one per CU) gets whole tiles of rows to
-// stream.  (Fewer codebooks or columns would leave half of the products on
-// padding; such tables fit the gather-fused kernel, which takes them: the
-// 131072 x 64 output of a 32-codebook layer in 19 against 31 us.)
-constexpr int64_t kMaccMinRows = 16384;
+// C % 16 == 0, C <= 128, M % 4 == 0 and M >= 16, a 4-byte aligned table, 8-byte
+// aligned index rows and 16-byte aligned outputs, unless the gather-fused
+// kernel can take the table in 16-byte units (C divides 64, it fits in LDS and
+// M % 16 == 0: a 131072 x 64 output of 32 codebooks in 19 against 31 us).  Every row count: against the
+// gathers it replaces, 64 x 512 outputs take 11 against 22 us at 1 row and 12
+// against 24 at 2048, 128 x 4096 27 against 100-340 at 2048, 32 x 512 10
+// against 20 at 8192 and 115 against 177 at 262144.
 bool macc_shape(const Shape& s) {   // (everything but the index rows' alignment)
-  if (s.elem != kI8 || s.C % 16 != 0 || s.C < 48 || s.C > 128 || s.M % 4 != 0 || s.M < 128) return false;
-  if (s.N < kMaccMinRows) return false;
+  if (s.elem != kI8 || s.C % 16 != 0 || s.C > 128 || s.M % 4 != 0 || s.M < 16) return false;
   if (!aligned(s.lut, 4)) return false;
   if ((s.y && !aligned(s.y, 16)) || (s.acc && !aligned(s.acc, 16))) return false;
   return (int64_t)s.C * kK * s.M < (1ll << 31);
 }
 bool plan_macc(const Shape& s, MArgs* m, int* blocks_out) {
   if (!macc_shape(s) || !aligned(s.idx_in, 8)) return false;
-  const int W = macc_width(s.C);
+  GArgs g;
+  int gng, guq, gnw;
+  if (plan_gfused(s, &g, &gng, &guq, &gnw) && g.vec16) return false;
+  const int cp = macc_staged(s.C);
+  // 64 columns per slice, or 32 where then every wavefront still has at most
+  // one 64-row tile: half as much to stage, more workgroups.  (32 against 64
+  // columns: 64 x 512 outputs 11.3 against 12.8 us at 128 rows, 14.4 against
+  // 14.9 at 8192, 18.6 against 18.3 at 16384, 506 against 426 at 1M; 128 x 4096
+  // 22.2 against 22.7 at 1024 rows, 29.8 against 27.5 at 2048.  128 columns, for
+  // C <= 64: 18.2 us at 128 rows, 434 at 1M.)
+  const int cus = device_cus();
+  const int64_t tiles64 = (s.N + 63) / 64;
+  int W = 32, groups = 0;
+  for (;; W = 64) {
+    groups = cus / ((s.M + W - 1) / W);
+    if (groups < 1) groups = 1;
+    if (groups > tiles64) groups = (int)tiles64;
+    if (W == 64 || (tiles64 + groups - 1) / groups <= 8) break;
+  }
   MArgs a{};
   a.idx = s.idx_in; a.lut = static_cast<const int8_t*>(s.lut); a.scale = s.scale; a.offset = s.offset;
   a.y = s.y; a.acc = s.acc; a.col_bias = s.col_bias;
   a.N = s.N; a.C = s.C; a.M = s.M;
   a.act = s.act == 3 ? 1 : s.act;   // the softmax as a second pass
   a.bias_lds = (a.act != 0 && s.col_bias) ? 1 : 0;
+  a.W = W;
   a.nslices = (s.M + W - 1) / W;
-  int groups = device_cus() / a.nslices;
-  if (groups < 1) groups = 1;
   a.xcd_map = (groups * a.nslices) % 8 == 0;
-  a.rows_per_group = round_up64((s.N + groups - 1) / groups, 64);
+  a.rows_per_group = (tiles64 + groups - 1) / groups * 64;
   if (a.rows_per_group * s.M * 4 >= (1ll << 31)) return false;   // a group's outputs: 32-bit store offsets
-  int off = (s.C <= 64 ? 64 : 128) * W * 16;   // the transposed table slice
+  int off = cp * W * 16;   // the transposed table slice
   auto take = [&](int bytes) { const int o = off; off += round_up(bytes, 16); return o; };
-  const int cp = s.C <= 64 ? 64 : 128;
   a.off_val = take(kMaccGroups * cp);
   a.off_sh = take(4 * cp);
   a.off_misc = take(16);
@@ -653,17 +668,30 @@ int two_phase(const Shape& s, uint8_t* idx, hipStream_t stream) {
   return accumulate(q, stream);
 }
 
-// Whether a fused call that the row-streaming kernel could take runs faster
-// as encode + the one-hot product, through an index array: measured on 1M
-// rows of 512 columns of A with 64 codebooks, 0.84 against 1.05 ms at 512
-// output columns, 0.62 against 0.94 at 256, 0.51 against 0.89 at 128 (the
-// encode alone is 0.37 ms).  Not for a row softmax, which the row-streaming
-// kernel fuses and the two-phase path runs as a pass of its own.
-constexpr int kTwoPhaseMinCols = 128;
+// Whether a fused call that could run as one launch runs faster as encode +
+// the one-hot product, through an index array.  Not for a row softmax, which
+// the single-launch kernels fuse and the two-phase path runs as a pass of its
+// own.
+//  * The row-streaming kernel's shapes, from kTwoPhaseMinCols columns: on 1M
+//    rows of 512 columns of A with 64 codebooks, 0.84 against 1.05 ms at 512
+//    output columns, 0.62 against 0.94 at 256, 0.51 against 0.89 at 128 (the
+//    encode alone is 0.37 ms).
+//  * The general kernel's, and the gather-fused kernel's where it would stage
+//    the table element by element, from kTwoPhaseMinTable entries per prototype
+//    (C M): 64 x 100 outputs 17 against 22 us at 300 rows, 29 against 64 at
+//    30000, 80 against 204 at 131072; 48 x 100 16 / 25 / 69 against 19 / 61 /
+//    202; 32 x 100 12 against 14 at 300 rows.  Below (64 x 20: about 15 against
+//    13 us at 300 rows) the second launch costs more than it gains.
+constexpr int kTwoPhaseMinCols = 128, kTwoPhaseMinTable = 3072;
 bool two_phase_faster(const Shape& s) {
+  if (s.act == 3 || !macc_shape(s)) return false;
   FArgs f;
   int blocks;
-  return s.act != 3 && s.M >= kTwoPhaseMinCols && macc_shape(s) && plan_fenc(s, &f, &blocks, nullptr, 0);
+  if (plan_fenc(s, &f, &blocks, nullptr, 0)) return s.M >= kTwoPhaseMinCols;
+  GArgs g;
+  int ng, uq, nw;
+  if (plan_gfused(s, &g, &ng, &uq, &nw) && g.vec16) return false;
+  return s.C * s.M >= kTwoPhaseMinTable;
 }
 
 // Whether a fused call runs as one launch (the gather-fused kernel, or the
@@ -691,6 +719,10 @@ int fused(const Shape& s, hipStream_t st) {
   GArgs g;
   int ng, uq, nw;
   Plan p;
+  // (given an index array some shapes go faster in two phases; without one
+  // they run as one launch)
+  const bool two = s.idx_out && aligned(s.idx_out, 8) && two_phase_faster(s);
+  if (two) return two_phase(s, s.idx_out, st);
   const bool gf = plan_gfused(s, &g, &ng, &uq, &nw);
   if (gf && !g.vec16 && s.act == 0 && plan(s, &p, true) == MADDNESS_OK)
     return status_from(launch_path(s.mode, s.elem, p.pf, p.uq, p.a, p.grid, p.block, st));
@@ -698,10 +730,7 @@ int fused(const Shape& s, hipStream_t st) {
   FArgs f;
   TArgs t;
   int blocks;
-  // (given an index array the row-streaming kernel's shapes may go faster
-  // in two phases; without one they take that kernel, as one launch)
-  const bool two = s.idx_out && aligned(s.idx_out, 8) && two_phase_faster(s);
-  if (!two && plan_fenc(s, &f, &blocks, &t, device_cus())) {
+  if (plan_fenc(s, &f, &blocks, &t, device_cus())) {
     const int rc = status_from(launch_fenc(f, blocks, st));
     if (rc != MADDNESS_OK) return rc;
     return status_from(launch_trow(kI8, t, device_cus(), st));

@@ -189,11 +189,11 @@ struct MArgs {
   int64_t N, rows_per_group;   // rows_per_group: a multiple of 64
   int C, M, act;          // act: 0 none, 1 bias, 2 bias + ReLU (a softmax runs as a second pass)
   int bias_lds;           // column biases staged in LDS (act != 0 and col_bias given)
-  int nslices, xcd_map;
+  int W, nslices, xcd_map;   // W: columns per slice (32 or 64)
   int off_val, off_sh, off_misc, off_bias, lds_total;   // LDS byte offsets (the table slice at 0)
 };
 constexpr int kMaccGroups = 5;   // one-hot shift groups of 7 for shifts up to 30
-int macc_width(int C);
+int macc_staged(int C);   // codebooks its table slice is padded to (C % 16 == 0, C <= 128)
 hipError_t launch_macc(const MArgs& m, int blocks, hipStream_t stream);
 
 // Rounded 8-bit summation over codebooks: the whole [C][16][Mt] column slice

@@ -27,7 +27,7 @@
 // LDS once per 64 rows.
 //
 // Layout.  A workgroup (8 wavefronts) owns one column slice of W = 32 WB
-// columns for its lifetime, staged once into LDS transposed, as [codebook]
+// columns (32 for few rows, else 64) for its lifetime, staged once into LDS transposed, as [codebook]
 // [column][16 prototypes] bytes, so the table operand of a product (32
 // columns x 64 K values) is two 16-byte reads per lane.  Each wavefront takes
 // tiles of 64 rows (two 32-row blocks) of the workgroup's row range
@@ -159,6 +159,51 @@ __global__ void __launch_bounds__(kMWaves * 64) macc_kernel(const MArgs a) {
   if (r0 >= N) return;   // uniform: no rows for this workgroup
   const int64_t r1 = min(N, r0 + a.rows_per_group);
 
+  // ---------------- the table slice, transposed: LDS byte (c W + m) 16 + p =
+  // q[c][p][col0 + m].  A unit is 4 prototypes x 4 columns of one codebook:
+  // four dword loads (one per prototype row) and a 4 x 4 byte transpose.  A
+  // thread has kUnits of them and loads kUB at a time (one at a time, the
+  // prologue was a chain of 16 memory latencies); the first batch is requested
+  // before anything waits.
+  constexpr int kUnits = CP * W / (kMWaves * 64);
+  constexpr int kUB = kUnits % 4 == 0 ? 4 : kUnits % 3 == 0 ? 3 : kUnits;
+  static_assert(CP * W % (kMWaves * 64) == 0 && kUnits % kUB == 0, "whole batches");
+  uint32_t d0[kUB][4];
+  auto load_tab_units = [&](int ub, uint32_t (&d)[kUB][4]) {
+#pragma unroll
+    for (int i = 0; i < kUB; ++i) {
+      const int u = tid + (ub + i) * kMWaves * 64;
+      const int col = col0 + 4 * (u % (W / 4));
+      const int pg = (u / (W / 4)) & 3;
+      const int c = u / (W / 4) / 4;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t e = ((int64_t)c * 16 + 4 * pg + r) * M + col;
+        d[i][r] = (c < C && col < M) ? *reinterpret_cast<const uint32_t*>(a.lut + e) : 0u;
+      }
+    }
+  };
+  auto put_tab = [&](int ub, const uint32_t (&dd)[kUB][4]) {
+#pragma unroll
+    for (int i = 0; i < kUB; ++i) {
+      const int u = tid + (ub + i) * kMWaves * 64;
+      const int m4 = u % (W / 4);
+      const int pg = (u / (W / 4)) & 3;
+      const int c = u / (W / 4) / 4;
+      const uint32_t(&d)[4] = dd[i];
+      const uint32_t lo01 = __builtin_amdgcn_perm(d[1], d[0], 0x05010400u);   // d0.0 d1.0 d0.1 d1.1
+      const uint32_t hi01 = __builtin_amdgcn_perm(d[1], d[0], 0x07030602u);   // d0.2 d1.2 d0.3 d1.3
+      const uint32_t lo23 = __builtin_amdgcn_perm(d[3], d[2], 0x05010400u);
+      const uint32_t hi23 = __builtin_amdgcn_perm(d[3], d[2], 0x07030602u);
+      mlds_u32* dst = reinterpret_cast<mlds_u32*>(s_tab + ((c * W + 4 * m4) * 16 + 4 * pg));
+      dst[0] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);    // column + 0: d0.0 d1.0 d2.0 d3.0
+      dst[4] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);    // column + 1
+      dst[8] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);    // column + 2
+      dst[12] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);   // column + 3
+    }
+  };
+  load_tab_units(0, d0);
+
   // ---------------- block exponents, shifts, the offsets' sum
   if (tid == 0) { s_misc[1] = INT_MAX; s_misc[2] = 0; }
   __syncthreads();
@@ -183,31 +228,13 @@ __global__ void __launch_bounds__(kMWaves * 64) macc_kernel(const MArgs a) {
   if (a.bias_lds)   // zeros past the last column
     for (int m = tid; m < W; m += kMWaves * 64) s_bias[m] = col0 + m < M ? a.col_bias[col0 + m] : 0.0f;
 
-  // ---------------- the table slice, transposed: LDS byte (c W + m) 16 + p =
-  // q[c][p][col0 + m].  A unit is 4 prototypes x 4 columns of one codebook:
-  // four dword loads (one per prototype row) and a 4 x 4 byte transpose.
+  // ---------------- the table slice into LDS, the next batch's loads behind it
   {
-    constexpr int units = CP * 4 * (W / 4);
-    for (int u = tid; u < units; u += kMWaves * 64) {
-      const int m4 = u % (W / 4);
-      const int pg = (u / (W / 4)) & 3;
-      const int c = u / (W / 4) / 4;
-      const int col = col0 + 4 * m4;
-      uint32_t d[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t e = ((int64_t)c * 16 + 4 * pg + r) * M + col;
-        d[r] = (c < C && col < M) ? *reinterpret_cast<const uint32_t*>(a.lut + e) : 0u;
-      }
-      const uint32_t lo01 = __builtin_amdgcn_perm(d[1], d[0], 0x05010400u);   // d0.0 d1.0 d0.1 d1.1
-      const uint32_t hi01 = __builtin_amdgcn_perm(d[1], d[0], 0x07030602u);   // d0.2 d1.2 d0.3 d1.3
-      const uint32_t lo23 = __builtin_amdgcn_perm(d[3], d[2], 0x05010400u);
-      const uint32_t hi23 = __builtin_amdgcn_perm(d[3], d[2], 0x07030602u);
-      mlds_u32* dst = reinterpret_cast<mlds_u32*>(s_tab + ((c * W + 4 * m4) * 16 + 4 * pg));
-      dst[0] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);    // column + 0: d0.0 d1.0 d2.0 d3.0
-      dst[4] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);    // column + 1
-      dst[8] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);    // column + 2
-      dst[12] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);   // column + 3
+    put_tab(0, d0);
+#pragma unroll 1
+    for (int ub = kUB; ub < kUnits; ub += kUB) {
+      load_tab_units(ub, d0);
+      put_tab(ub, d0);
     }
   }
   __syncthreads();
@@ -448,20 +475,28 @@ __global__ void __launch_bounds__(kMWaves * 64) macc_kernel(const MArgs a) {
   }
 }
 
-int macc_width(int C) { return C <= 64 ? 128 : 64; }
+int macc_staged(int C) { return C <= 64 ? C : C <= 96 ? 96 : 128; }
 
 hipError_t launch_macc(const MArgs& m, int blocks, hipStream_t stream) {
-  const void* fn = m.C <= 64 ? reinterpret_cast<const void*>(&macc_kernel<4, 4>)
-                             : reinterpret_cast<const void*>(&macc_kernel<8, 2>);
+  void (*fn)(MArgs) = nullptr;
+  switch (macc_staged(m.C) / 16 * 2 + (m.W == 64)) {
+    case 2: fn = macc_kernel<1, 1>; break;
+    case 3: fn = macc_kernel<1, 2>; break;
+    case 4: fn = macc_kernel<2, 1>; break;
+    case 5: fn = macc_kernel<2, 2>; break;
+    case 6: fn = macc_kernel<3, 1>; break;
+    case 7: fn = macc_kernel<3, 2>; break;
+    case 8: fn = macc_kernel<4, 1>; break;
+    case 9: fn = macc_kernel<4, 2>; break;
+    case 12: fn = macc_kernel<6, 1>; break;
+    case 13: fn = macc_kernel<6, 2>; break;
+    case 16: fn = macc_kernel<8, 1>; break;
+    default: fn = macc_kernel<8, 2>; break;
+  }
   hipError_t err = hipSuccess;
-  launch_prepare(fn, kMWaves * 64, m.lds_total, &err);
+  launch_prepare(reinterpret_cast<const void*>(fn), kMWaves * 64, m.lds_total, &err);
   if (err != hipSuccess) return err;
-  if (m.C <= 64)
-    hipLaunchKernelGGL((macc_kernel<4, 4>), dim3((unsigned)blocks), dim3(kMWaves * 64), m.lds_total,
-                       stream, m);
-  else
-    hipLaunchKernelGGL((macc_kernel<8, 2>), dim3((unsigned)blocks), dim3(kMWaves * 64), m.lds_total,
-                       stream, m);
+  hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(kMWaves * 64), m.lds_total, stream, m);
   return hipGetLastError();
 }
 

@@ -1,0 +1,63 @@
+"""The one-hot product from one row up: every codebook padding (16 to 128 in
+steps of 16), both slice widths (32 columns while every wavefront has at most
+one 64-row tile, else 64), rows and columns around the tiles, several shift
+groups, and the fused calls that take it when they are given an index array and
+a single launch when they are not.  Sums, outputs and indices bit-exact."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2207_05808_amd as mdn
+from paper_2207_05808_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).to(DEV)
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+@pytest.mark.parametrize("N,C,M,max_shift", [(1, 16, 16, 0), (31, 16, 1028, 8), (33, 32, 100, 3), (64, 48, 36, 14),
+                                             (65, 64, 132, 2), (577, 64, 96, 6), (130, 80, 64, 7), (1000, 96, 32, 1),
+                                             (1025, 112, 4100, 3), (513, 128, 2052, 1), (4097, 32, 516, 5),
+                                             (9000, 16, 640, 9), (70000, 64, 20, 1), (33000, 48, 68, 2)])
+def test_accumulate(orc, N, C, M, max_shift):
+    lut, scale, offset = W.random_codes(C, M, seed=N + C, max_shift=max_shift)
+    idx = W.random_indices(N, C, seed=N)
+    acc, y = mdn.lut_accumulate(dev(idx), dev(lut), dev(scale), dev(offset), want_acc=True)
+    _, y1 = mdn.lut_accumulate(dev(idx), dev(lut), dev(scale), dev(offset))
+    racc, ry = orc.lut_accumulate(idx, lut, scale, offset)
+    assert np.array_equal(host(acc), racc) and np.array_equal(host(y), ry) and np.array_equal(host(y1), ry)
+
+
+@pytest.mark.parametrize("N,D,C,M", [(1, 64, 32, 100), (300, 130, 48, 64), (2000, 512, 64, 100), (777, 96, 96, 32),
+                                     (5000, 64, 16, 200)])
+@pytest.mark.parametrize("act", ["none", "relu"])
+def test_fused_with_and_without_indices(orc, N, D, C, M, act):
+    """The two routes of one call: through an index array and as one launch."""
+    rng = np.random.default_rng(N + C)
+    A = rng.standard_normal((N, D)).astype(np.float32)
+    split = rng.integers(0, D, (C, 4)).astype(np.int32)
+    thr = rng.standard_normal((C, 15)).astype(np.float32)
+    lut, scale, offset = W.random_codes(C, M, seed=C, max_shift=2)
+    bias = rng.standard_normal(M).astype(np.float32)
+    args = [dev(x) for x in (A, split, thr, lut, scale, offset)]
+    ridx, _, ry = orc.matmul(A, split, thr, lut, scale, offset)
+    assert mdn.matmul_index_bytes(args[0], C, M, act=act) == N * C
+    idx = torch.empty((N, C), dtype=torch.uint8, device=DEV)
+    if act == "none":
+        y, _, _ = mdn.matmul(*args, idx_out=idx)
+        one = torch.empty((N, M), dtype=torch.float32, device=DEV)
+        mdn.matmul_noalloc(*args, one)
+        assert np.array_equal(host(one), ry)
+    else:
+        y = mdn.matmul_act(*args, col_bias=dev(bias), act=act, idx_out=idx)
+        z = ry + bias
+        ry = np.where(z > 0, z, np.float32(0))
+    assert np.array_equal(host(idx), ridx) and np.array_equal(host(y), ry)
