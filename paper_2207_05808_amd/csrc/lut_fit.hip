@@ -18,10 +18,9 @@
 //           sums the bucket's rows in that order: every entry is the
 //           sum of its rows in ascending row order.
 //   solve   A = H + lambda I (double), B = R + lambda T0; A = L L^T by a
-//           blocked right-looking Cholesky factorisation (panels of 32:
-//           diagonal block in one workgroup, the rows below it, then the
-//           trailing update), then blocked forward and backward substitution
-//           over the M columns of B, in place.
+//           blocked right-looking Cholesky factorisation (panels of 32: the
+//           panel, then the trailing update), then blocked forward and
+//           backward substitution over the M columns of B, in place.
 // Every multiply-subtract is one fused multiply-add, and every entry takes
 // its terms in the same order as the unblocked algorithm (k ascending in the
 // factor and forward pass, descending in the backward pass), so the result
@@ -382,179 +381,257 @@ assemble_kernel(const int32_t* __restrict__ H, int64_t n, double lam, double* __
 }
 
 // ---------------------------------------------------------- factorisation
-// diagonal block [j0, j0 + jb) of the panel: unblocked right-looking in LDS
-__global__ void __launch_bounds__(256) potrf_diag_kernel(double* __restrict__ A, int64_t n, int j0, int jb) {
-  __shared__ double a[kNB][kNB + 1];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < kNB * kNB; e += 256) {
-    const int i = e / kNB, j = e % kNB;
-    a[i][j] = (i < jb && j <= i) ? A[(j0 + i) * n + j0 + j] : 0.0;
-  }
-  __syncthreads();
-  for (int j = 0; j < jb; ++j) {
-    if (tid == 0) a[j][j] = __dsqrt_rn(a[j][j]);
-    __syncthreads();
-    const double d = a[j][j];
-    for (int i = j + 1 + tid; i < jb; i += 256) a[i][j] = __ddiv_rn(a[i][j], d);
-    __syncthreads();
-    // update of the columns right of j: entry (i, q), j < q <= i, term k = j
-    for (int e = tid; e < kNB * kNB; e += 256) {
-      const int i = e / kNB, q = e % kNB;
-      if (q > j && q <= i && i < jb) a[i][q] = __fma_rn(-a[i][j], a[q][j], a[i][q]);
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < kNB * kNB; e += 256) {
-    const int i = e / kNB, j = e % kNB;
-    if (i < jb && j <= i) A[(j0 + i) * n + j0 + j] = a[i][j];
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// v's lane `from` (uniform), in every lane
+__device__ __forceinline__ double lane_of(double v, int from) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, from);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), from);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// Panel [j0, j0 + jb): the diagonal block's factor and the rows below it,
+// L21 = A21 L11^-T, in one launch.  A wavefront holds the 32 rows of the
+// diagonal block (lanes 0-31) and 32 rows below (lanes 32-63), a row of 32
+// columns per lane, and factors the block along with its own rows: every
+// wavefront repeats the block, none waits for another.  Right-looking, term
+// k = column; after each column the row moves down one register, so that 8
+// columns share one short loop body.  The block's factor goes to `diag`
+// ([32][32], row-major): other wavefronts may still be reading the block, the
+// trailing update's launch puts it in its place.  (No rows below: directly.)
+// Bound: the chain of 32 square roots and divisions, about 250 cycles a column
+// with the update of the next one: 14.5 us, against 21 us for the block in one
+// workgroup with two barriers a column and then 18 us for the rows (21 us with
+// the factors through readlane).
+//
+// The next pivot is lane j + 1's own value, so its square root starts at once;
+// the column's other factors go round through LDS (s_c, aligned to the column,
+// so they are read 16 bytes at a time, the same address in every lane).
+// `root`: the square root of column j's pivot, kept from column to column.
+template <int W>
+__device__ __forceinline__ void panel_columns(double (&x)[kNB], double& root, int j, int j1, int lane, double* s_out,
+                                              double* s_c) {
+#pragma unroll 1
+  for (; j < j1; ++j) {
+    const double v = lane == j ? root : __ddiv_rn(x[0], root);
+    s_out[lane * (kNB + 1) + j] = v;
+    s_c[(lane - j - 1) & 63] = v;   // lane j + q at q - 1
+    root = __dsqrt_rn(lane_of(__fma_rn(-v, v, x[1]), j + 1));
+    // (the wavefront's own LDS, in order)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 1; q <= W; ++q) x[q - 1] = __fma_rn(-v, s_c[q - 1], x[q]);
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
-// rows [j0 + jb, n) of the panel: L21 = A21 L11^-T, one row per thread
-__global__ void __launch_bounds__(256) trsm_panel_kernel(double* __restrict__ A, int64_t n, int j0, int jb) {
-  __shared__ double l[kNB][kNB + 1];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < kNB * kNB; e += 256) {
-    const int i = e / kNB, j = e % kNB;
-    l[i][j] = (i < jb && j <= i) ? A[(j0 + i) * n + j0 + j] : 0.0;
-  }
-  __syncthreads();
-  const int64_t row = (int64_t)j0 + jb + (int64_t)blockIdx.x * 256 + tid;
-  if (row >= n) return;
-  double* ar = A + row * n + j0;
+constexpr int kPanelWaves = 2;
+__global__ void __launch_bounds__(kPanelWaves * 64)
+panel_kernel(double* __restrict__ A, int64_t n, int j0, int jb, double* __restrict__ diag) {
+  __shared__ double s_out[kPanelWaves][64 * (kNB + 1)];
+  __shared__ __attribute__((aligned(16))) double s_col[kPanelWaves][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t w = (int64_t)blockIdx.x * kPanelWaves + wave;
+  const int64_t below = (int64_t)j0 + jb + w * 32;   // first own row
+  if (w > 0 && below >= n) return;
+  const bool top = lane < 32;
+  const int64_t row = top ? j0 + lane : below + lane - 32;
+  const bool ok = top ? lane < jb : row < n;
+  const double* ar = A + (ok ? row : j0) * n + j0;
   double x[kNB];
 #pragma unroll
-  for (int j = 0; j < kNB; ++j) x[j] = j < jb ? ar[j] : 0.0;
-#pragma unroll
-  for (int j = 0; j < kNB; ++j) {
-    if (j < jb) {
-      x[j] = __ddiv_rn(x[j], l[j][j]);
-#pragma unroll
-      for (int q = j + 1; q < kNB; ++q) x[q] = __fma_rn(-x[j], l[q][j], x[q]);
+  for (int j = 0; j < kNB; ++j) x[j] = ok && j < jb && (!top || j <= lane) ? ar[j] : 0.0;
+  double* so = s_out[wave];
+  double* sc = s_col[wave];
+  double root = __dsqrt_rn(lane_of(x[0], 0));
+  panel_columns<31>(x, root, 0, 8, lane, so, sc);
+  panel_columns<23>(x, root, 8, 16, lane, so, sc);
+  if (jb > 16) {
+    panel_columns<15>(x, root, 16, 24, lane, so, sc);
+    panel_columns<7>(x, root, 24, 32, lane, so, sc);
+  }
+  // (a wavefront's own LDS, in order)
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const bool only = (int64_t)j0 + jb >= n;
+  for (int e = lane; e < 64 * kNB; e += 64) {
+    const int r = e / kNB, j = e % kNB;
+    const double v = so[r * (kNB + 1) + j];
+    if (r < 32) {
+      if (w == 0 && r < jb && j <= r) {
+        if (only) A[(j0 + r) * n + j0 + j] = v;
+        else diag[r * kNB + j] = v;
+      }
+    } else if (below + r - 32 < n && j < jb) {
+      A[(below + r - 32) * n + j0 + j] = v;
     }
   }
-#pragma unroll
-  for (int j = 0; j < kNB; ++j)
-    if (j < jb) ar[j] = x[j];
 }
 
-// trailing update: A[i][q] -= sum_{k in panel, ascending} L[i][k] L[q][k] for
-// j0 + jb <= q <= i < n; a 32 x 32 tile per workgroup (lower tiles only)
-__global__ void __launch_bounds__(256) syrk_kernel(double* __restrict__ A, int64_t n, int j0, int jb) {
-  __shared__ double li[kNB][kNB + 1];
-  __shared__ double lq[kNB][kNB + 1];
-  const int tid = threadIdx.x;
+// Trailing update: A[i][q] -= sum_{k in panel, ascending} L[i][k] L[q][k] for
+// j0 + 32 <= q <= i < n (a panel with rows below it has all 32 columns); a 32 x
+// 32 tile per workgroup (lower tiles only), 16 x 16 per wavefront, on the fp64
+// matrix instruction: it takes its 4 terms k ascending, one fused multiply-add
+// each (found equal to that chain bit for bit), so a tile's 32 terms are the
+// unblocked algorithm's.  Lane l holds row (or column) l % 16 and term l / 16
+// of the operands, column l % 16 and rows l / 16 + 4 r of the result; all loads
+// go out together and no LDS is used: 4.6-7.6 us for n = 1024 against 7.5-10
+// staged through LDS with 4 chains a thread.
+__global__ void __launch_bounds__(256)
+syrk_kernel(double* __restrict__ A, int64_t n, int j0, const double* __restrict__ diag) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // tile (ti, tq), ti >= tq, from the linear block index
   int ti = 0;
   const int b = blockIdx.x;
   while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
   const int tq = b - ti * (ti + 1) / 2;
-  const int64_t s = (int64_t)j0 + jb;
-  const int64_t i0 = s + (int64_t)ti * kNB, q0 = s + (int64_t)tq * kNB;
-  for (int e = tid; e < kNB * kNB; e += 256) {
-    const int r = e / kNB, k = e % kNB;
-    li[r][k] = (i0 + r < n && k < jb) ? A[(i0 + r) * n + j0 + k] : 0.0;
-    lq[r][k] = (q0 + r < n && k < jb) ? A[(q0 + r) * n + j0 + k] : 0.0;
-  }
-  __syncthreads();
-  const int ty = tid / 16, tx = tid % 16;
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int r = ty + 16 * a, q = tx + 16 * c;
-      const int64_t gi = i0 + r, gq = q0 + q;
-      if (gi < n && gq <= gi) {
-        double v = A[gi * n + gq];
-        for (int k = 0; k < jb; ++k) v = __fma_rn(-li[r][k], lq[q][k], v);
-        A[gi * n + gq] = v;
-      }
+  const int64_t s = (int64_t)j0 + kNB;
+  if (b == 0)   // the diagonal block's factor into its place
+    for (int e = threadIdx.x; e < kNB * kNB; e += 256) {
+      const int i = e / kNB, j = e % kNB;
+      if (j <= i) A[(j0 + i) * n + j0 + j] = diag[e];
     }
+  const int64_t i0 = s + (int64_t)ti * kNB + 16 * (wave >> 1), q0 = s + (int64_t)tq * kNB + 16 * (wave & 1);
+  if (i0 >= n || q0 > i0 + 15) return;   // (n is a multiple of 16)
+  const int lr = lane & 15, lk = lane >> 4;
+  const double* li = A + (i0 + lr) * n + j0 + lk;
+  const double* lq = A + (q0 + lr) * n + j0 + lk;
+  double va[kNB / 4], vb[kNB / 4];
+  f64x4 c;
+#pragma unroll
+  for (int k = 0; k < kNB / 4; ++k) {
+    va[k] = li[4 * k];
+    vb[k] = lq[4 * k];
+  }
+  double* out = A + (i0 + lk) * n + q0 + lr;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) c[r] = out[4 * r * n];
+#pragma unroll
+  for (int k = 0; k < kNB / 4; ++k) c = __builtin_amdgcn_mfma_f64_16x16x4f64(-va[k], vb[k], c, 0, 0, 0);
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (q0 + lr <= i0 + lk + 4 * r) out[4 * r * n] = c[r];
 }
 
 // ------------------------------------------------------------------ solves
 // B [n][M] in place.  Forward: z_i = (b_i - sum_{k < i} L[i][k] z_k) / L[i][i],
 // k ascending; backward: t_i = (z_i - sum_{k > i} L[k][i] t_k) / L[i][i], k
-// descending.  Blocks of 32 rows; the diagonal block one column per thread,
-// the update of the other rows as 32 x 64 tiles.
-template <bool FWD>
-__global__ void __launch_bounds__(256) trsv_diag_kernel(const double* __restrict__ A, int64_t n, double* __restrict__ B,
-                                                         int M, int i0, int ib) {
-  __shared__ double l[kNB][kNB + 1];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < kNB * kNB; e += 256) {
-    const int i = e / kNB, j = e % kNB;
-    l[i][j] = (i < ib && j <= i) ? A[(i0 + i) * n + i0 + j] : 0.0;
+// descending.  Blocks of 32 rows; launch `i0` takes the terms of block i0
+// (solved) to every row block still to come, 32 rows x 64 columns per
+// workgroup, and the workgroups of the next block solve it at once, so a block
+// costs one launch.  The terms go through the fp64 matrix instruction (k
+// ascending inside it; the backward pass hands it the terms in reverse).
+// i0 < 0: no terms, the first block is solved.
+//
+// Bound: launches and the solve's chain of 32 divisions: 11 us a block (n 1024,
+// 512 columns) against 23 us for a launch of the solve and one of the terms.
+constexpr int kTvCols = 64;
+
+template <int W>
+__device__ __forceinline__ void solve_rows(double (&x)[kNB], int i, int i1, const double (*s_l)[kNB], const double* s_d,
+                                           double* __restrict__ out, int64_t step, bool ok) {
+#pragma unroll 1
+  for (; i < i1; ++i) {
+    double l[W];   // (read before the division, which they do not wait for)
+#pragma unroll
+    for (int q = 0; q < W; ++q) l[q] = s_l[i][q];
+    const double v = __ddiv_rn(x[0], s_d[i]);
+    if (ok) out[i * step] = v;
+#pragma unroll
+    for (int q = 1; q <= W; ++q) x[q - 1] = __fma_rn(-l[q - 1], v, x[q]);
   }
-  __syncthreads();
-  const int64_t m = (int64_t)blockIdx.x * 256 + tid;
-  if (m >= M) return;
-  double x[kNB];
-#pragma unroll
-  for (int i = 0; i < kNB; ++i) x[i] = i < ib ? B[(i0 + i) * (int64_t)M + m] : 0.0;
-  if (FWD) {
-#pragma unroll
-    for (int i = 0; i < kNB; ++i) {
-      if (i < ib) {
-        x[i] = __ddiv_rn(x[i], l[i][i]);
-#pragma unroll
-        for (int q = i + 1; q < kNB; ++q) x[q] = __fma_rn(-l[q][i], x[i], x[q]);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int i = kNB - 1; i >= 0; --i) {
-      if (i < ib) {
-        x[i] = __ddiv_rn(x[i], l[i][i]);
-#pragma unroll
-        for (int q = 0; q < i; ++q) x[q] = __fma_rn(-l[i][q], x[i], x[q]);
-      }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < kNB; ++i)
-    if (i < ib) B[(i0 + i) * (int64_t)M + m] = x[i];
 }
 
-// FWD: rows r >= i0 + ib get the block's terms, k ascending: b_r -= L[r][k] z_k.
-// !FWD: rows r < i0 get them, k descending: b_r -= L[k][r] t_k.
 template <bool FWD>
-__global__ void __launch_bounds__(256) trsv_update_kernel(const double* __restrict__ A, int64_t n, double* __restrict__ B,
-                                                           int M, int i0, int ib) {
-  __shared__ double lr[kNB][kNB + 1];   // lr[r][k]: the coefficient of block row k in row r
-  __shared__ double z[kNB][64];
-  const int tid = threadIdx.x;
-  const int ntm = (M + 63) / 64;
-  const int64_t r0 = FWD ? (int64_t)i0 + ib + (int64_t)(blockIdx.x / ntm) * kNB : (int64_t)(blockIdx.x / ntm) * kNB;
-  const int64_t rend = FWD ? n : i0;
-  const int64_t m0 = (int64_t)(blockIdx.x % ntm) * 64;
-  for (int e = tid; e < kNB * kNB; e += 256) {
-    const int r = e / kNB, k = e % kNB;
-    const int64_t gr = r0 + r;
-    double v = 0.0;
-    if (gr < rend && k < ib) v = FWD ? A[gr * n + i0 + k] : A[(i0 + k) * n + gr];
-    lr[r][k] = v;
-  }
-  for (int e = tid; e < kNB * 64; e += 256) {
-    const int k = e / 64, c = e % 64;
-    z[k][c] = (k < ib && m0 + c < M) ? B[(i0 + k) * (int64_t)M + m0 + c] : 0.0;
-  }
-  __syncthreads();
-  const int c = tid % 64;
-  const int rr = tid / 64;   // rows rr, rr + 4, ..., 8 per thread
-  if (m0 + c >= M) return;
+__global__ void __launch_bounds__(256)
+trsv_kernel(const double* __restrict__ A, int64_t n, double* __restrict__ B, int M, int64_t i0, int ib, int64_t next0) {
+  __shared__ double s_z[kNB][kTvCols];
+  __shared__ __attribute__((aligned(16))) double s_l[kNB][kNB];   // [i][q - 1]: the factor of unknown i in unknown i + q
+  __shared__ double s_d[kNB];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ntm = (M + kTvCols - 1) / kTvCols;
+  // row blocks: forward next0, next0 + 32, ...; backward next0, next0 - 32, ...
+  const int64_t r0 = FWD ? next0 + (int64_t)(blockIdx.x / ntm) * kNB : next0 - (int64_t)(blockIdx.x / ntm) * kNB;
+  const int64_t m0 = (int64_t)(blockIdx.x % ntm) * kTvCols;
+  const bool solve = r0 == next0;   // uniform
+  const int rb = (int)(n - r0 < kNB ? n - r0 : kNB);   // 16 or 32 rows
+  const int lr = lane & 15, lk = lane >> 4;
+  const int64_t col = m0 + 16 * wave + lr;
+  const bool cok = col < M;
+  const int64_t cc = cok ? col : M - 1;
+  // every load first: the terms' operands, the rows, and for the solve the
+  // block's factor (unknown i of the block is row i forward, row rb - 1 - i
+  // backward)
+  f64x4 c[2];
+  double va[2][kNB / 4], vb[kNB / 4], f[kNB * kNB / 256], fd = 1.0;
+  double* out = B + (r0 + lk) * M + cc;
 #pragma unroll
-  for (int a = 0; a < kNB / 4; ++a) {
-    const int r = rr + 4 * a;
-    const int64_t gr = r0 + r;
-    if (gr >= rend) continue;
-    double v = B[gr * (int64_t)M + m0 + c];
-    if (FWD) {
-      for (int k = 0; k < ib; ++k) v = __fma_rn(-lr[r][k], z[k][c], v);
-    } else {
-      for (int k = ib - 1; k >= 0; --k) v = __fma_rn(-lr[r][k], z[k][c], v);
+  for (int k = 0; k < kNB / 4; ++k) {
+    const int t = FWD ? 4 * k + lk : ib - 1 - (4 * k + lk);   // term: row i0 + t of the solved block
+    const bool tok = i0 >= 0 && t >= 0 && t < ib;
+    const int64_t gk = tok ? i0 + t : 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t gr = 16 * h < rb ? r0 + 16 * h + lr : r0;
+      va[h][k] = tok ? (FWD ? A[gr * n + gk] : A[gk * n + gr]) : 0.0;
     }
-    B[gr * (int64_t)M + m0 + c] = v;
+    vb[k] = tok ? B[gk * (int64_t)M + cc] : 0.0;
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) c[h][r] = 16 * h < rb ? out[(16 * h + 4 * r) * (int64_t)M] : 0.0;
+  if (solve) {
+#pragma unroll
+    for (int u = 0; u < kNB * kNB / 256; ++u) {
+      const int e = tid + 256 * u, i = e / kNB, q = e % kNB + 1;
+      f[u] = i + q >= rb ? 0.0
+             : FWD       ? A[(r0 + i + q) * n + r0 + i]
+                         : A[(r0 + rb - 1 - i) * n + r0 + rb - 1 - i - q];
+    }
+    if (tid < rb) fd = A[(r0 + (FWD ? tid : rb - 1 - tid)) * (n + 1)];
+  }
+  if (i0 >= 0) {
+#pragma unroll
+    for (int k = 0; k < kNB / 4; ++k)
+      if (4 * k < ib)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) c[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(-va[h][k], vb[k], c[h], 0, 0, 0);
+  }
+  if (solve) {
+#pragma unroll
+    for (int u = 0; u < kNB * kNB / 256; ++u) s_l[(tid + 256 * u) / kNB][(tid + 256 * u) % kNB] = f[u];
+    if (tid < kNB) s_d[tid] = fd;
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (solve)
+        s_z[16 * h + lk + 4 * r][16 * wave + lr] = c[h][r];
+      else if (cok && 16 * h < rb)
+        out[(16 * h + 4 * r) * (int64_t)M] = c[h][r];
+    }
+  if (!solve) return;
+  __syncthreads();
+  if (wave != 0) return;
+  double x[kNB];
+#pragma unroll
+  for (int i = 0; i < kNB; ++i) x[i] = i < rb ? s_z[FWD ? i : rb - 1 - i][lane] : 0.0;
+  const int64_t m = m0 + lane;
+  const bool ok = m < M;
+  double* z = B + (FWD ? r0 : r0 + rb - 1) * (int64_t)M + (ok ? m : 0);
+  const int64_t step = FWD ? M : -(int64_t)M;
+  solve_rows<31>(x, 0, 8, s_l, s_d, z, step, ok);
+  solve_rows<23>(x, 8, 16, s_l, s_d, z, step, ok);
+  if (rb > 16) {
+    solve_rows<15>(x, 16, 24, s_l, s_d, z, step, ok);
+    solve_rows<7>(x, 24, 32, s_l, s_d, z, step, ok);
   }
 }
 
@@ -787,36 +864,36 @@ hipError_t launch_fit_ridge(const uint8_t* idx, int64_t N, int C, const float* Y
   hipLaunchKernelGGL(assemble_kernel, dim3(grid_1d(n * n, 256)), dim3(256), 0, stream, H, n, lam, A, T, T0,
                      n * M);
   if ((e = hipGetLastError()) != hipSuccess) return e;
+  // (the counts are not read any more: their array holds a panel's diagonal
+  // block, 8 KB, when the panel has rows below it, n >= 48)
+  double* diag = reinterpret_cast<double*>(H);
   for (int j0 = 0; j0 < n; j0 += kNB) {
     const int jb = (int)((n - j0) < kNB ? (n - j0) : kNB);
-    hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(256), 0, stream, A, n, j0, jb);
     const int64_t below = n - j0 - jb;
+    const int64_t waves = below > 0 ? (below + 31) / 32 : 1;
+    hipLaunchKernelGGL(panel_kernel, dim3((unsigned)((waves + kPanelWaves - 1) / kPanelWaves)), dim3(kPanelWaves * 64), 0,
+                       stream, A, n, j0, jb, diag);
     if (below > 0) {
-      hipLaunchKernelGGL(trsm_panel_kernel, dim3(grid_1d(below, 256)), dim3(256), 0, stream, A, n, j0, jb);
       const int64_t tiles = (below + kNB - 1) / kNB;
-      hipLaunchKernelGGL(syrk_kernel, dim3((unsigned)(tiles * (tiles + 1) / 2)), dim3(256), 0, stream, A, n, j0,
-                         jb);
+      hipLaunchKernelGGL(syrk_kernel, dim3((unsigned)(tiles * (tiles + 1) / 2)), dim3(256), 0, stream, A, n, j0, diag);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  const int ntm = (M + 63) / 64;
-  for (int i0 = 0; i0 < n; i0 += kNB) {   // forward
-    const int ib = (int)((n - i0) < kNB ? (n - i0) : kNB);
-    hipLaunchKernelGGL(trsv_diag_kernel<true>, dim3(grid_1d(M, 256)), dim3(256), 0, stream, A, n, T, M, i0, ib);
-    const int64_t below = n - i0 - ib;
-    if (below > 0)
-      hipLaunchKernelGGL(trsv_update_kernel<true>, dim3((unsigned)(((below + kNB - 1) / kNB) * ntm)), dim3(256), 0,
-                         stream, A, n, T, M, i0, ib);
+  const int64_t ntm = (M + kTvCols - 1) / kTvCols;
+  const int64_t last = ((n - 1) / kNB) * kNB;
+  for (int64_t i0 = -kNB; i0 < last; i0 += kNB) {   // forward: block i0's terms, block i0 + 32 solved
+    const int64_t next0 = i0 + kNB;
+    const int64_t blocks = i0 < 0 ? 1 : (n - next0 + kNB - 1) / kNB;
+    hipLaunchKernelGGL(trsv_kernel<true>, dim3((unsigned)(blocks * ntm)), dim3(256), 0, stream, A, n, T, M, i0, kNB,
+                       next0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  const int64_t last = ((n - 1) / kNB) * kNB;
-  for (int64_t i0 = last; i0 >= 0; i0 -= kNB) {   // backward
-    const int ib = (int)((n - i0) < kNB ? (n - i0) : kNB);
-    hipLaunchKernelGGL(trsv_diag_kernel<false>, dim3(grid_1d(M, 256)), dim3(256), 0, stream, A, n, T, M, (int)i0,
-                       ib);
-    if (i0 > 0)
-      hipLaunchKernelGGL(trsv_update_kernel<false>, dim3((unsigned)(((i0 + kNB - 1) / kNB) * ntm)), dim3(256), 0,
-                         stream, A, n, T, M, (int)i0, ib);
+  for (int64_t next0 = last; next0 >= 0; next0 -= kNB) {   // backward: block next0 + 32's terms, block next0 solved
+    const int64_t i0 = next0 == last ? -1 : next0 + kNB;
+    const int ib = (int)(i0 >= 0 && n - i0 < kNB ? n - i0 : kNB);
+    const int64_t blocks = i0 < 0 ? 1 : next0 / kNB + 1;
+    hipLaunchKernelGGL(trsv_kernel<false>, dim3((unsigned)(blocks * ntm)), dim3(256), 0, stream, A, n, T, M, i0, ib,
+                       next0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
