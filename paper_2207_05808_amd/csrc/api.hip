@@ -204,17 +204,17 @@ int plan(const Shape& s, Plan* out, bool single_tile_only) {
 
 // Gather-fused plan: C divides 64 and the whole table (plus one zero row,
 // staged as int16 for int8 tables) fits in LDS.  Returns false when the
-// shape does not qualify.
-bool plan_gfused(const Shape& s, GArgs* g, int* ng_out, int* uq_out, int* nw_out) {
+// shape does not qualify.  With `cus` = 0 (planning without a HIP call) the
+// split for many rows; it qualifies the same shapes.
+bool plan_gfused(const Shape& s, GArgs* g, int* ng_out, int* uq_out, int* nw_out, int cus = 0) {
   if (s.C > 64 || (64 % s.C) != 0) return false;
   int nw = 16;   // one 1024-thread workgroup per CU stages the table once
   const int G = 64 / s.C;
   const int no = (s.M + 7) / 8;   // column octets
   int best_ng = 0, best_uq = 0, best_lpr = 0;
   int64_t best_cost = 0;
-  for (int ng = 1; ng <= 4; ng *= 2) {
+  auto consider = [&](int ng) {
     const int R = ng * G;
-    if (R > 64) break;
     for (int uq = 1; uq <= 4; uq *= 2) {
       int lpr = 1;
       while (lpr < 64 && lpr * uq < no) lpr *= 2;
@@ -227,8 +227,32 @@ bool plan_gfused(const Shape& s, GArgs* g, int* ng_out, int* uq_out, int* nw_out
         best_ng = ng; best_uq = uq_eff; best_lpr = lpr; best_cost = cost;
       }
     }
-  }
+  };
+  for (int ng = 1; ng <= 4 && ng * G <= 64; ng *= 2) consider(ng);
   if (best_ng == 0) return false;
+  const bool vec16 = aligned(s.lut, 16) && (s.elem == kF32 ? (s.M % 4 == 0) : (s.M % 16 == 0));
+  // Few rows: fewer per wavefront, and half as many wavefronts per workgroup
+  // where the table still takes at most 4 16-byte units per thread, so that the
+  // call spreads over as many workgroups as there are CUs (a wavefront's 4
+  // gathers, a walk and a sum are then all a row costs).  The fewest rows per
+  // wavefront that leave at most one workgroup per CU, never more than above.
+  // 3x3-conv layer (C 32, M
+  // 64), 1 / 2 / 4 row groups and 8 wavefronts, against 4 and 16: 1024 rows 6.6 /
+  // 7.0 / 8.9 against 12.9 us, 4096 7.1 / 7.5 / 9.3 against 13.1, 8192 9.9 / 8.4 /
+  // 9.7 against 13.5, 16384 14.3 / 12.8 / 12.5 against 17.0; more rows keep 4
+  // groups and 16 wavefronts.
+  if (cus > 0) {
+    const int64_t units = (int64_t)s.C * kK * s.M * (s.elem == kF32 ? 4 : 1) / 16;
+    const int few = vec16 && units <= 4 * 512 ? 8 : 16;
+    for (int ng = 1, most = best_ng; ng <= most; ng *= 2) {
+      const int64_t steps = (s.N + ng * G - 1) / (ng * G);
+      if ((steps + few - 1) / few > cus) continue;
+      nw = few;
+      best_ng = 0;
+      consider(ng);
+      break;
+    }
+  }
   GArgs a{};
   a.A = s.A; a.split = s.split; a.thr = s.thr; a.lut = s.lut; a.scale = s.scale; a.offset = s.offset;
   a.y = s.y; a.acc = s.acc; a.idx_out = s.idx_out;
@@ -241,7 +265,7 @@ bool plan_gfused(const Shape& s, GArgs* g, int* ng_out, int* uq_out, int* nw_out
   a.NSP = round_up(s.C, 4);
   a.lpr_log2 = ilog2(best_lpr);
   a.vec_out = (s.M % 4 == 0) && aligned(s.y, 16) && (s.acc == nullptr || aligned(s.acc, 16));
-  a.vec16 = aligned(s.lut, 16) && (s.elem == kF32 ? (s.M % 4 == 0) : (s.M % 16 == 0));
+  a.vec16 = vec16;
   a.col_bias = s.col_bias;
   a.act = s.act;
   if ((int64_t)a.R * s.lda * 4 >= (1ll << 31)) return false;   // 32-bit per-lane gather offsets
@@ -612,7 +636,7 @@ int accumulate(const Shape& s, hipStream_t stream) {
     // index loads in place of the encode
     GArgs g;
     int ng, uq, gnw;
-    if (plan_gfused(s, &g, &ng, &uq, &gnw)) {
+    if (plan_gfused(s, &g, &ng, &uq, &gnw, device_cus())) {
       g.idx_in = s.idx_in;
       return status_from(launch_gfused(s.elem, ng, uq, g, gnw, device_cus(), stream));
     }
@@ -723,7 +747,7 @@ int fused(const Shape& s, hipStream_t st) {
   // they run as one launch)
   const bool two = s.idx_out && aligned(s.idx_out, 8) && two_phase_faster(s);
   if (two) return two_phase(s, s.idx_out, st);
-  const bool gf = plan_gfused(s, &g, &ng, &uq, &nw);
+  const bool gf = plan_gfused(s, &g, &ng, &uq, &nw, device_cus());
   if (gf && !g.vec16 && s.act == 0 && plan(s, &p, true) == MADDNESS_OK)
     return status_from(launch_path(s.mode, s.elem, p.pf, p.uq, p.a, p.grid, p.block, st));
   if (gf) return status_from(launch_gfused(s.elem, ng, uq, g, nw, device_cus(), st));
