@@ -19,7 +19,8 @@ __all__ = list(_BINDING) + ["MaddnessError"]
 def __getattr__(name):
     if name in _BINDING:
         from . import binding
-        return getattr(binding, name)
+        globals()[name] = value = getattr(binding, name)   # found directly from now on
+        return value
     if name == "MaddnessError":
         from ._lib import MaddnessError
         return MaddnessError

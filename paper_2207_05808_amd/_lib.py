@@ -11,6 +11,8 @@ single HIP runtime (torch's), which the library then binds to by soname.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch  # noqa: F401  (must precede loading libmaddness.so, see module doc)
@@ -78,6 +80,28 @@ def lib() -> ctypes.CDLL:
             getattr(L, f).restype = ctypes.c_int
         _lib = L
     return _lib
+
+
+_calls = None
+
+
+def calls():
+    """The native marshalling of the fused calls (csrc/torch_calls.cpp), bound
+    to the library that is loaded; raises if it has not been built."""
+    global _calls
+    if _calls is None:
+        path = os.path.join(_HERE, "_calls.so")
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} is missing: build it with paper_2207_05808_amd.build.build()")
+        loader = importlib.machinery.ExtensionFileLoader("_calls", path)
+        m = importlib.util.module_from_spec(importlib.util.spec_from_loader("_calls", loader))
+        loader.exec_module(m)
+        L = lib()
+        m.init(*(ctypes.cast(getattr(L, f), ctypes.c_void_p).value for f in (
+            "maddness_matmul", "maddness_matmul_f32", "maddness_matmul_act", "maddness_matmul_act_f32",
+            "maddness_matmul_index_bytes")))
+        _calls = m
+    return _calls
 
 
 def check(fn: str, status: int) -> None:

@@ -55,6 +55,26 @@ def _rows(A: torch.Tensor) -> Tuple[int, int, int]:
     return N, D, lda
 
 
+def _native(A, split, thr, lut, scale, offset, col_bias, act, y_out, acc_out, idx_out, want_acc, want_idx):
+    """The call marshalled natively, on the current stream: (y, acc, idx), or
+    None when the arguments are not the plain valid case (the caller then goes
+    through its own checks, which raise) or the call reports an error."""
+    if type(A) is not torch.Tensor or not A.is_cuda or not (act is None or type(act) is int):
+        return None
+    fused = _fused or _load_native()
+    return fused(A, split, thr, lut, scale, offset, col_bias, act, y_out, acc_out, idx_out, want_acc, want_idx,
+                 torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+
+
+_fused = None
+
+
+def _load_native():
+    global _fused
+    _fused = _lib.calls().fused
+    return _fused
+
+
 def _tree_args(split: torch.Tensor, thr: torch.Tensor) -> int:
     _need(split, "split_dims", torch.int32, 2)
     _need(thr, "thresholds", torch.float32, 2)
@@ -187,6 +207,10 @@ def lut_accumulate_f32(idx, lut, y_out=None, stream=None, validate=False):
 def matmul(A, split_dims, thresholds, lut, scale, offset, y_out=None, acc_out=None, idx_out=None,
            want_acc=False, want_idx=False, stream=None, validate=False):
     """Fused encode + int8 lookup-accumulate; returns (y, acc or None, idx or None)."""
+    if stream is None and validate is False and scale is not None:
+        r = _native(A, split_dims, thresholds, lut, scale, offset, None, None, y_out, acc_out, idx_out, want_acc, want_idx)
+        if r is not None:
+            return r
     N, D, lda = _rows(A)
     C = _tree_args(split_dims, thresholds)
     C2, M = _lut_i8(lut, scale, offset)
@@ -242,6 +266,10 @@ def matmul_noalloc(A, split_dims, thresholds, lut, scale, offset, y_out, acc_out
 def matmul_f32(A, split_dims, thresholds, lut, y_out=None, idx_out=None, want_idx=False, stream=None,
                validate=False):
     """Fused encode + fp32 lookup-accumulate; returns (y, idx or None)."""
+    if stream is None and validate is False:
+        r = _native(A, split_dims, thresholds, lut, None, None, None, None, y_out, None, idx_out, False, want_idx)
+        if r is not None:
+            return r[0], r[2]
     N, D, lda = _rows(A)
     C = _tree_args(split_dims, thresholds)
     _need(lut, "lut", torch.float32, 3)
@@ -274,6 +302,11 @@ def _act(act):
             raise ValueError(f"act must be one of {sorted(ACT)}")
         return ACT[act]
     return int(act)
+
+
+def _act_code(act):
+    """act as an int, or something _native declines (never None)."""
+    return ACT.get(act, "") if isinstance(act, str) else "" if act is None else act
 
 
 def _col_bias(col_bias, M):
@@ -329,6 +362,11 @@ def matmul_act(A, split_dims, thresholds, lut, scale, offset, col_bias=None, act
     "relu" / "softmax"; "bias" or "none" also accepted); returns y.  With
     idx_out the indices are written there; without it an index array is
     allocated here when the shape needs one (matmul_index_bytes)."""
+    if stream is None and validate is False and scale is not None:
+        r = _native(A, split_dims, thresholds, lut, scale, offset, col_bias, _act_code(act), y_out, None, idx_out,
+                    False, False)
+        if r is not None:
+            return r[0]
     N, D, lda = _rows(A)
     C = _tree_args(split_dims, thresholds)
     C2, M = _lut_i8(lut, scale, offset)
@@ -354,6 +392,11 @@ def matmul_act(A, split_dims, thresholds, lut, scale, offset, col_bias=None, act
 def matmul_act_f32(A, split_dims, thresholds, lut, col_bias=None, act="relu", y_out=None, idx_out=None,
                    stream=None, validate=False):
     """matmul_act over an unquantized fp32 table; returns y."""
+    if stream is None and validate is False:
+        r = _native(A, split_dims, thresholds, lut, None, None, col_bias, _act_code(act), y_out, None, idx_out,
+                    False, False)
+        if r is not None:
+            return r[0]
     N, D, lda = _rows(A)
     C = _tree_args(split_dims, thresholds)
     _need(lut, "lut", torch.float32, 3)

@@ -1,9 +1,10 @@
 """Build libmaddness.so for gfx950 in-tree with hipcc (always recompiles).
 
 Each source is compiled to an object in its own hipcc process (in parallel),
-then the objects are linked into the shared library.  Kernels are launched
-only from the translation unit that defines them, so no relocatable device
-code is needed.
+then the objects are linked into the shared library.  _calls.so, the native
+marshalling of the binding's fused calls, is compiled beside them.  Kernels
+are launched only from the translation unit that defines them, so no
+relocatable device code is needed.
 """
 from __future__ import annotations
 
@@ -35,6 +36,19 @@ def _run(cmd):
     return r.returncode, errs
 
 
+def _calls_cmd(out: str):
+    """The host compiler's line for the native marshalling of torch calls
+    (csrc/torch_calls.cpp): a CPython extension against torch's own headers."""
+    import sysconfig
+    import torch
+    t = os.path.dirname(torch.__file__)
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unknown-pragmas",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+            "-isystem", sysconfig.get_paths()["include"], os.path.join(HERE, "csrc", "torch_calls.cpp"),
+            "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", out]
+
+
 def build(verbose: bool = False, jobs: int = 0) -> str:
     out = os.path.join(HERE, "libmaddness.so")
     tmp = out + ".tmp"
@@ -49,11 +63,13 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
         if verbose:
             for c in cmds:
                 print(" ".join(c), flush=True)
+        calls = os.path.join(HERE, "_calls.so")
+        cmds.append(_calls_cmd(calls + ".tmp"))
         with ThreadPoolExecutor(max_workers=jobs) as ex:
             results = list(ex.map(_run, cmds))
         for (rc, errs), c in zip(results, cmds):
             if rc != 0:
-                raise RuntimeError(f"hipcc failed ({rc}) on {c[-3]}:\n{errs}")
+                raise RuntimeError(f"compiler failed ({rc}) on {' '.join(c)}:\n{errs}")
             if verbose and errs.strip():
                 print(errs, file=sys.stderr)
         link = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp]
@@ -63,6 +79,7 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
         if rc != 0:
             raise RuntimeError(f"link failed ({rc}):\n{errs}")
     os.replace(tmp, out)
+    os.replace(calls + ".tmp", calls)
     return out
 
 

@@ -1,0 +1,180 @@
+// One call of a fused entry point on torch tensors, marshalled natively.
+//
+// The Python binding checks every argument attribute by attribute and builds
+// the argument list through ctypes, about 14 us of host time per call, more
+// than twice the kernel time of the small layers (1024 x 64 -> 10, C 4:
+// 14.8 -> 5.1 us a call).  `fused(...)` does the same for the
+// plain valid case only (exact torch.Tensor arguments, device memory, the
+// documented dtypes and shapes, dense outputs) and returns None for anything
+// else, an error included: the binding then takes its own path, which raises
+// what it always raised.  No arithmetic of the method happens here.
+//
+// The library's functions come in as addresses (`init`), from the library the
+// ctypes binding has loaded: there is one copy of it in the process.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+#include <ATen/ATen.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <stdint.h>
+
+namespace {
+
+typedef int (*MatmulFn)(const float*, int64_t, int32_t, int64_t, const int32_t*, const float*, int32_t, const int8_t*,
+                        const float*, const float*, int32_t, float*, int32_t*, uint8_t*, void*);
+typedef int (*MatmulF32Fn)(const float*, int64_t, int32_t, int64_t, const int32_t*, const float*, int32_t, const float*,
+                           int32_t, float*, uint8_t*, void*);
+typedef int (*ActFn)(const float*, int64_t, int32_t, int64_t, const int32_t*, const float*, int32_t, const int8_t*,
+                     const float*, const float*, int32_t, const float*, int32_t, float*, uint8_t*, void*);
+typedef int (*ActF32Fn)(const float*, int64_t, int32_t, int64_t, const int32_t*, const float*, int32_t, const float*,
+                        int32_t, const float*, int32_t, float*, uint8_t*, void*);
+typedef int64_t (*IndexBytesFn)(const float*, int64_t, int32_t, int64_t, int32_t, int32_t, int32_t, int32_t);
+
+MatmulFn g_matmul;
+MatmulF32Fn g_matmul_f32;
+ActFn g_act;
+ActF32Fn g_act_f32;
+IndexBytesFn g_index_bytes;
+
+PyObject* init(PyObject*, PyObject* args) {
+  unsigned long long a, b, c, d, e;
+  if (!PyArg_ParseTuple(args, "KKKKK", &a, &b, &c, &d, &e)) return nullptr;
+  g_matmul = reinterpret_cast<MatmulFn>(a);
+  g_matmul_f32 = reinterpret_cast<MatmulF32Fn>(b);
+  g_act = reinterpret_cast<ActFn>(c);
+  g_act_f32 = reinterpret_cast<ActF32Fn>(d);
+  g_index_bytes = reinterpret_cast<IndexBytesFn>(e);
+  Py_RETURN_NONE;
+}
+
+// the tensor behind an exact torch.Tensor (no subclass) in device memory of
+// this type and rank; nullptr otherwise
+const at::Tensor* plain(PyObject* o, at::ScalarType type, int64_t dim) {
+  if (!THPVariable_CheckExact(o)) return nullptr;
+  const at::Tensor& t = THPVariable_Unpack(o);
+  if (!t.defined() || t.layout() != at::kStrided || !t.is_cuda() || t.scalar_type() != type || t.dim() != dim ||
+      !t.has_storage())
+    return nullptr;
+  return &t;
+}
+const at::Tensor* dense(PyObject* o, at::ScalarType type, int64_t dim) {
+  const at::Tensor* t = plain(o, type, dim);
+  return t && t->is_contiguous() ? t : nullptr;
+}
+
+// fused(A, split, thr, lut, scale, offset, col_bias, act, y_out, acc_out,
+// idx_out, want_acc, want_idx, stream) -> (y, acc, idx) or None.  scale and
+// offset None: an fp32 table.  act None: the entry points without a layer
+// output.
+PyObject* fused(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  if (n != 14 || !g_matmul) Py_RETURN_NONE;
+  try {
+    const bool f32 = a[4] == Py_None && a[5] == Py_None;
+    const at::Tensor* A = plain(a[0], at::kFloat, 2);
+    const at::Tensor* split = dense(a[1], at::kInt, 2);
+    const at::Tensor* thr = dense(a[2], at::kFloat, 2);
+    const at::Tensor* lut = dense(a[3], f32 ? at::kFloat : at::kChar, 3);
+    if (!A || !split || !thr || !lut) Py_RETURN_NONE;
+    const int64_t N = A->size(0), D = A->size(1), C = split->size(0), M = lut->size(2);
+    if (N > 1 && A->stride(1) != 1) Py_RETURN_NONE;
+    const int64_t lda = N > 1 ? A->stride(0) : D;
+    if (split->size(1) != 4 || thr->size(0) != C || thr->size(1) != 15 || lut->size(0) != C || lut->size(1) != 16)
+      Py_RETURN_NONE;
+    if (N <= 0 || D <= 0 || C <= 0 || M <= 0 || lda < D || D > INT32_MAX || C > INT32_MAX || M > INT32_MAX)
+      Py_RETURN_NONE;
+    const at::Tensor *scale = nullptr, *offset = nullptr, *bias = nullptr;
+    if (!f32) {
+      scale = dense(a[4], at::kFloat, 1);
+      offset = dense(a[5], at::kFloat, 1);
+      if (!scale || !offset || scale->size(0) != C || offset->size(0) != C) Py_RETURN_NONE;
+    }
+    if (a[6] != Py_None) {
+      bias = dense(a[6], at::kFloat, 1);
+      if (!bias || bias->size(0) != M) Py_RETURN_NONE;
+    }
+    const long act = a[7] == Py_None ? -1 : PyLong_AsLong(a[7]);
+    const bool want_acc = a[11] == Py_True, want_idx = a[12] == Py_True;
+    void* stream = PyLong_AsVoidPtr(a[13]);
+    if (PyErr_Occurred()) {
+      PyErr_Clear();
+      Py_RETURN_NONE;
+    }
+    if (act > 3 || (act < 0 && a[7] != Py_None)) Py_RETURN_NONE;
+    // outputs: the caller's, when they are what a new one would be, else new
+    // (checked before any is allocated)
+    const at::Tensor *y_in = nullptr, *acc_in = nullptr, *idx_in = nullptr;
+    if (a[8] != Py_None && !((y_in = dense(a[8], at::kFloat, 2)) && y_in->size(0) == N && y_in->size(1) == M))
+      Py_RETURN_NONE;
+    if (a[9] != Py_None && !((acc_in = dense(a[9], at::kInt, 2)) && acc_in->size(0) == N && acc_in->size(1) == M))
+      Py_RETURN_NONE;
+    if (a[10] != Py_None && !((idx_in = dense(a[10], at::kByte, 2)) && idx_in->size(0) == N && idx_in->size(1) == C))
+      Py_RETURN_NONE;
+    const auto opt = A->options().requires_grad(false);
+    at::Tensor y = y_in ? *y_in : at::empty({N, M}, opt);
+    at::Tensor acc, idx, scratch;
+    if (acc_in) acc = *acc_in;
+    else if (want_acc) acc = at::empty({N, M}, opt.dtype(at::kInt));
+    if (idx_in) idx = *idx_in;
+    else if (want_idx) idx = at::empty({N, C}, opt.dtype(at::kByte));
+    const float* pA = static_cast<const float*>(A->const_data_ptr());
+    if (!idx.defined() && g_index_bytes(pA, N, (int32_t)D, lda, (int32_t)C, (int32_t)M, f32, act < 0 ? 0 : (int32_t)act) > 0)
+      scratch = at::empty({N, C}, opt.dtype(at::kByte));
+    uint8_t* pi = idx.defined()       ? static_cast<uint8_t*>(idx.mutable_data_ptr())
+                  : scratch.defined() ? static_cast<uint8_t*>(scratch.mutable_data_ptr())
+                                      : nullptr;
+    const int32_t* ps = static_cast<const int32_t*>(split->const_data_ptr());
+    const float* pt = static_cast<const float*>(thr->const_data_ptr());
+    const void* pl = lut->const_data_ptr();
+    const float* psc = scale ? static_cast<const float*>(scale->const_data_ptr()) : nullptr;
+    const float* pof = offset ? static_cast<const float*>(offset->const_data_ptr()) : nullptr;
+    const float* pb = bias ? static_cast<const float*>(bias->const_data_ptr()) : nullptr;
+    float* py = static_cast<float*>(y.mutable_data_ptr());
+    int32_t* pacc = acc.defined() ? static_cast<int32_t*>(acc.mutable_data_ptr()) : nullptr;
+    int rc;
+    Py_BEGIN_ALLOW_THREADS
+    if (act < 0)
+      rc = f32 ? g_matmul_f32(pA, N, (int32_t)D, lda, ps, pt, (int32_t)C, static_cast<const float*>(pl), (int32_t)M, py, pi,
+                              stream)
+               : g_matmul(pA, N, (int32_t)D, lda, ps, pt, (int32_t)C, static_cast<const int8_t*>(pl), psc, pof, (int32_t)M,
+                          py, pacc, pi, stream);
+    else
+      rc = f32 ? g_act_f32(pA, N, (int32_t)D, lda, ps, pt, (int32_t)C, static_cast<const float*>(pl), (int32_t)M, pb,
+                           (int32_t)act, py, pi, stream)
+               : g_act(pA, N, (int32_t)D, lda, ps, pt, (int32_t)C, static_cast<const int8_t*>(pl), psc, pof, (int32_t)M, pb,
+                       (int32_t)act, py, pi, stream);
+    Py_END_ALLOW_THREADS
+    if (rc != 0) Py_RETURN_NONE;
+    auto out = [](PyObject* given, const at::Tensor& t) -> PyObject* {
+      if (given != Py_None) {
+        Py_INCREF(given);
+        return given;
+      }
+      if (!t.defined()) Py_RETURN_NONE;
+      return THPVariable_Wrap(t);
+    };
+    PyObject* r = PyTuple_New(3);
+    if (!r) return nullptr;
+    PyTuple_SET_ITEM(r, 0, out(a[8], y));
+    PyTuple_SET_ITEM(r, 1, out(a[9], acc));
+    PyTuple_SET_ITEM(r, 2, out(a[10], idx));
+    for (int i = 0; i < 3; ++i)
+      if (!PyTuple_GET_ITEM(r, i)) {
+        Py_DECREF(r);
+        return nullptr;
+      }
+    return r;
+  } catch (...) {   // (a tensor without plain memory, out of device memory, ...): the binding's own path says what
+    PyErr_Clear();
+    Py_RETURN_NONE;
+  }
+}
+
+PyMethodDef methods[] = {
+    {"init", init, METH_VARARGS, "addresses of the library's functions"},
+    {"fused", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(fused)), METH_FASTCALL, "one fused call"},
+    {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__calls() { return PyModule_Create(&module); }
