@@ -159,6 +159,28 @@ __global__ void __launch_bounds__(kMWaves * 64) macc_kernel(const MArgs a) {
   if (r0 >= N) return;   // uniform: no rows for this workgroup
   const int64_t r1 = min(N, r0 + a.rows_per_group);
 
+  // ---------------- the first tile's index rows, requested before anything waits
+  const int h = lane >> 5;    // half-wavefront: codebook 16 j + 8 h + i of the pair
+  const int ml = lane & 31;   // table operand: column; one-hot operand and results: row
+  const int cvalid = (C + 15) >> 4;   // index chunks of 16 codebooks that exist
+  const int64_t ntiles = (r1 - r0 + kMTileRows - 1) / kMTileRows;
+  // index bytes of codebooks 16 j + 8 h .. + 7 of the lane's two rows
+  auto load_idx = [&](int64_t t, mu32x2 (&ix)[2][C16]) {
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) {
+      int64_t row = r0 + t * kMTileRows + 32 * rb + ml;
+      row = row < N ? row : N - 1;
+      const uint8_t* src = a.idx + row * C + 8 * h;
+#pragma unroll
+      for (int j = 0; j < C16; ++j)
+        ix[rb][j] = j < cvalid ? *reinterpret_cast<const mu32x2*>(src + 16 * j) : (mu32x2){0u, 0u};
+    }
+  };
+
+  mu32x2 ixc[2][C16];
+  int64_t t = wave;
+  if (t < ntiles) load_idx(t, ixc);
+
   // ---------------- the table slice, transposed: LDS byte (c W + m) 16 + p =
   // q[c][p][col0 + m].  A unit is 4 prototypes x 4 columns of one codebook:
   // four dword loads (one per prototype row) and a 4 x 4 byte transpose.  A
@@ -217,11 +239,17 @@ __global__ void __launch_bounds__(kMWaves * 64) macc_kernel(const MArgs a) {
     atomicMax((int*)&s_misc[2], sh);
   }
   if (wave == 0) {   // double sum over codebooks in ascending order, rounded once
+    // (unrolled by 16, which C is a multiple of: the conversions run ahead of
+    // the chain of adds)
     double sum = 0.0;
     for (int c0 = 0; c0 < C; c0 += 64) {
       const float ov = a.offset[min(c0 + lane, C - 1)];
       const int n = min(64, C - c0);
-      for (int j = 0; j < n; ++j) sum += (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(ov), j));
+#pragma unroll 1
+      for (int j = 0; j < n; j += 16)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          sum += (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(ov), j + i));
     }
     if (lane == 0) s_misc[0] = __float_as_int((float)sum);
   }
@@ -252,28 +280,10 @@ __global__ void __launch_bounds__(kMWaves * 64) macc_kernel(const MArgs a) {
   const float bias32 = __int_as_float(muni(s_misc[0]));
 
   // ---------------- row tiles
-  const int h = lane >> 5;    // half-wavefront: codebook 16 j + 8 h + i of the pair
-  const int ml = lane & 31;   // table operand: column; one-hot operand and results: row
   const uint32_t lane_tab = (uint32_t)(uintptr_t)(s_tab + (h * W + ml) * 16);
-  const int cvalid = (C + 15) >> 4;   // index chunks of 16 codebooks that exist
-  const int64_t ntiles = (r1 - r0 + kMTileRows - 1) / kMTileRows;
-
-  // index bytes of codebooks 16 j + 8 h .. + 7 of the lane's two rows
-  auto load_idx = [&](int64_t t, mu32x2 (&ix)[2][C16]) {
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-      int64_t row = r0 + t * kMTileRows + 32 * rb + ml;
-      row = row < N ? row : N - 1;
-      const uint8_t* src = a.idx + row * C + 8 * h;
-#pragma unroll
-      for (int j = 0; j < C16; ++j)
-        ix[rb][j] = j < cvalid ? *reinterpret_cast<const mu32x2*>(src + 16 * j) : (mu32x2){0u, 0u};
-    }
-  };
 
   // index chunks of the current tile; chunk j is reloaded with the next
   // tile's as soon as the last product step that reads it has been issued
-  mu32x2 ixc[2][C16];
   const bool plain = a.y && !a.acc && col0 + W <= M;   // uniform
   const bool whole = a.y && col0 + W <= M;               // (the int32 sums too, whole tiles only)
   // the layer output of 4 consecutive columns from slice column lc: bias,
@@ -289,8 +299,6 @@ __global__ void __launch_bounds__(kMWaves * 64) macc_kernel(const MArgs a) {
     }
     return z;
   };
-  int64_t t = wave;
-  if (t < ntiles) load_idx(t, ixc);
   for (; t < ntiles; t += kMWaves) {
     const bool more = t + kMWaves < ntiles;   // uniform
     mi32x16 acc[2][WB];
