@@ -342,7 +342,11 @@ __device__ __forceinline__ void scatter_bucket(const int32_t* __restrict__ perm,
 }
 
 constexpr int kScCols = 64;                                            // columns of floats per workgroup
-constexpr int step_cols(int M) { return M <= 128 ? 16 : 32; }          // of doubles: 8 tiles, or the fewer LDS accesses
+// of doubles: at most 8 tiles of 16 for narrow layers (their chains are what
+// counts: 79 us against 86 with 32 columns, C 32, M 64), else 64 (the LDS is what
+// counts, and narrower tiles leave most of an access unused: C 256, M 1024 2.8 ms
+// a step against 6.9 with 32 columns)
+constexpr int step_cols(int M) { return M <= 128 ? 16 : 64; }
 unsigned scatter_grid(int C, int M, int cols) { return (unsigned)(C * kK * ((M + cols - 1) / cols)); }
 
 __global__ void __launch_bounds__(kScWaves * 64)
@@ -919,7 +923,7 @@ hipError_t launch_fit_gd(const uint8_t* idx, int64_t N, int C, const float* Y, i
       hipLaunchKernelGGL(resid, dim3(rows), dim3(256), 0, stream, idx, N, C, T, M, bias, act, P, D);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    auto step = step_cols(M) == 16 ? scatter_step_kernel<16> : scatter_step_kernel<32>;
+    auto step = step_cols(M) == 16 ? scatter_step_kernel<16> : scatter_step_kernel<64>;
     hipLaunchKernelGGL(step, dim3(scatter_grid(C, M, step_cols(M))), dim3(kScWaves * 64), 0, stream, perm,
                        start, N, C, D, M, T0, lam, eta, T);
     if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -1,7 +1,7 @@
 """The fit's bucket sums and gradient steps where their split can go wrong:
 bucket sizes around the stages of rows (56 and 224, in groups of 224 and 448),
 one bucket with every row and the others empty, column counts around the tiles
-(16, 32, 64) and around the residual kernels' forms (64, 128, 256 columns in
+(16, 64) and around the residual kernels' forms (64, 128, 256 columns in
 registers, more through memory), the sort's batches (64 rows, 8 at a time, 16
 wavefronts), infinities, NaN and signed zeros.  Bit-exact against the oracle:
 every sum takes its rows in ascending order on both sides.
