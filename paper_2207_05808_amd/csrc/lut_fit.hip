@@ -686,7 +686,9 @@ target_kernel(const float* __restrict__ Y, int64_t N, int M, const float* __rest
 // lane, lane + 64, ... (J of them; columns past M read column M - 1): the
 // indices come 64 codebooks at a time, one per lane, and are handed out
 // through readlane, so a table row's address is uniform and 8 codebooks' loads
-// are in flight.  n is uniform.
+// are in flight.  n and m0 are uniform and all 64 lanes are active: readlane
+// reads a lane's register also where the lane is not, and then finds what an
+// earlier call left there.
 template <int J>
 __device__ __forceinline__ void gather_row(const uint8_t* __restrict__ ir, int C, const double* __restrict__ T, int M,
                                            int m0, int lane, double (&s)[J]) {
@@ -786,11 +788,14 @@ resid_kernel(const uint8_t* __restrict__ idx, int64_t N, int C, const double* __
   for (int64_t n = (int64_t)blockIdx.x * 4 + wave; n < N; n += (int64_t)gridDim.x * 4) {
     double* dr = D + n * M;
     const double* pr = P + n * M;
-    for (int m = lane; m < M; m += 64) {
+    for (int m0 = 0; m0 < M; m0 += 64) {   // uniform: every lane takes part in gather_row
+      const int m = m0 + lane;
       double s[1];
-      gather_row<1>(idx + n * C, C, T, M, m - lane, lane, s);
-      const double z = __dadd_rn(s[0], bias ? (double)bias[m] : 0.0);
-      dr[m] = (act == 2) ? (z > 0.0 ? __dmul_rn(2.0, __dsub_rn(z, pr[m])) : 0.0) : z;
+      gather_row<1>(idx + n * C, C, T, M, m0, lane, s);
+      if (m < M) {
+        const double z = __dadd_rn(s[0], bias ? (double)bias[m] : 0.0);
+        dr[m] = (act == 2) ? (z > 0.0 ? __dmul_rn(2.0, __dsub_rn(z, pr[m])) : 0.0) : z;
+      }
     }
     if (act == 3) {
       softmax_row_inplace(dr, M, lane);

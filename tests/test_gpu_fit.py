@@ -126,7 +126,11 @@ def test_fit_on_workload_training_rows(orc, name):
 GD_CASES = [(200, 2, 5, 0.2, 1.0, 10, False),
             (700, 8, 64, 0.0, 0.5, 6, True),
             (1500, 17, 100, 1.0, 1.0, 5, True),
-            (999, 32, 10, 0.5, 1.5, 8, False)]
+            (999, 32, 10, 0.5, 1.5, 8, False),
+            # over 256 columns with a last part of fewer than 64, and more than 64 codebooks
+            (300, 70, 300, 0.3, 1.0, 3, True),
+            (200, 128, 257, 0.0, 0.5, 2, False),
+            (150, 96, 1000, 0.5, 1.0, 2, True)]
 
 
 def lipschitz(orc, idx, lam):
