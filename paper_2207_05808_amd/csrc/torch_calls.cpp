@@ -93,6 +93,9 @@ PyObject* fused(PyObject*, PyObject* const* a, Py_ssize_t n) {
       if (!bias || bias->size(0) != M) Py_RETURN_NONE;
     }
     const long act = a[7] == Py_None ? -1 : PyLong_AsLong(a[7]);
+    // other truth values (1, a numpy bool) are the binding's to judge
+    for (int i = 11; i <= 12; ++i)
+      if (a[i] != Py_True && a[i] != Py_False) Py_RETURN_NONE;
     const bool want_acc = a[11] == Py_True, want_idx = a[12] == Py_True;
     void* stream = PyLong_AsVoidPtr(a[13]);
     if (PyErr_Occurred()) {

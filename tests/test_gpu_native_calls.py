@@ -101,3 +101,17 @@ def test_other_callers(call):
         y2 = mdn.matmul(k["A"], *q)[0]
     torch.cuda.synchronize()
     assert same(y1, ref) and same(y2, ref)
+
+
+@pytest.mark.parametrize("yes,no", [(1, 0), (np.True_, np.False_), ("acc", None)])
+def test_truth_values(call, yes, no):
+    """want_acc and want_idx go by truth, whatever their type."""
+    k = call
+    t = (k["A"], k["split"], k["thr"])
+    q = (k["lut"], k["scale"], k["offset"])
+    ref = mdn.matmul(*t, *q, want_acc=True, want_idx=True)
+    assert same(mdn.matmul(*t, *q, want_acc=yes, want_idx=yes), ref)
+    assert same(mdn.matmul(*t, *q, want_acc=yes, want_idx=no), (ref[0], ref[1], None))
+    assert same(mdn.matmul(*t, *q, want_acc=no, want_idx=yes), (ref[0], None, ref[2]))
+    assert same(mdn.matmul_f32(*t, k["tab"], want_idx=yes)[1], ref[2])
+    assert mdn.matmul_f32(*t, k["tab"], want_idx=no)[1] is None
