@@ -706,16 +706,25 @@ int two_phase(const Shape& s, uint8_t* idx, hipStream_t stream) {
 //    30000, 80 against 204 at 131072; 48 x 100 16 / 25 / 69 against 19 / 61 /
 //    202; 32 x 100 12 against 14 at 300 rows.  Below (64 x 20: about 15 against
 //    13 us at 300 rows) the second launch costs more than it gains.
+// Only where the encode has a plan: it stages whole rows of A (D up to 4096 in
+// 16-byte units, else up to about 10,000), which the single launches need not.
 constexpr int kTwoPhaseMinCols = 128, kTwoPhaseMinTable = 3072;
 bool two_phase_faster(const Shape& s) {
   if (s.act == 3 || !macc_shape(s)) return false;
   FArgs f;
   int blocks;
-  if (plan_fenc(s, &f, &blocks, nullptr, 0)) return s.M >= kTwoPhaseMinCols;
-  GArgs g;
-  int ng, uq, nw;
-  if (plan_gfused(s, &g, &ng, &uq, &nw) && g.vec16) return false;
-  return s.C * s.M >= kTwoPhaseMinTable;
+  if (plan_fenc(s, &f, &blocks, nullptr, 0)) {
+    if (s.M < kTwoPhaseMinCols) return false;
+  } else {
+    GArgs g;
+    int ng, uq, nw;
+    if (plan_gfused(s, &g, &ng, &uq, &nw) && g.vec16) return false;
+    if (s.C * s.M < kTwoPhaseMinTable) return false;
+  }
+  Shape e = s;
+  e.mode = kEncode;
+  Plan p;
+  return plan(e, &p, false) == MADDNESS_OK;
 }
 
 // Whether a fused call runs as one launch (the gather-fused kernel, or the

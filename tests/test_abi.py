@@ -118,6 +118,21 @@ def test_matmul_index_bytes(L):
     assert Q(FAKE, 10, 64, 64, 600, 10, 0, 0) == -3           # too many codebooks
 
 
+def test_matmul_index_bytes_of_rows_the_encode_cannot_stage(L):
+    """Two phases need the encode, which stages whole rows of A: past its
+    widest (4096 columns in 16-byte units, about 10,000 otherwise) the calls
+    that can run as one launch do, and ask for no index array."""
+    Q = L.maddness_matmul_index_bytes
+    for C, M in ((32, 100), (64, 72)):
+        for act in (0, 2):
+            for D in (576, 4096, 4101):
+                assert Q(FAKE, 1000, D, D, C, M, 0, act) == 1000 * C
+            for D in (4100, 4608, 10300, 10301):
+                assert Q(FAKE, 1000, D, D, C, M, 0, act) == 0
+    for D, n in ((4096, 98304 * 64), (4100, 0), (4608, 0)):   # the row-streaming kernel's shapes
+        assert Q(FAKE, 98304, D, D, 64, 512, 0, 0) == n
+
+
 def test_fused_two_phase_needs_index_array(L):
     """Without idx_out a call whose table does not fit the single-launch
     kernels is rejected (EINVAL) before any HIP call: the library never

@@ -61,3 +61,47 @@ def test_fused_with_and_without_indices(orc, N, D, C, M, act):
         z = ry + bias
         ry = np.where(z > 0, z, np.float32(0))
     assert np.array_equal(host(idx), ridx) and np.array_equal(host(y), ry)
+
+
+@pytest.mark.parametrize("act", ["none", "relu"])
+@pytest.mark.parametrize("C,M", [(32, 100), (64, 72)])
+@pytest.mark.parametrize("D", [4096, 4100, 4608, 10300, 10301])
+def test_wide_rows(orc, D, C, M, act):
+    """Rows of A around and past the widest that the encode can stage, with and
+    without an index array."""
+    N = 130
+    rng = np.random.default_rng(D + C)
+    A = rng.standard_normal((N, D), dtype=np.float32)
+    split = rng.integers(0, D, (C, 4)).astype(np.int32)
+    split[0] = D - 1
+    thr = rng.standard_normal((C, 15), dtype=np.float32)
+    lut, scale, offset = W.random_codes(C, M, seed=D, max_shift=2)
+    ridx, racc, ry = orc.matmul(A, split, thr, lut, scale, offset)
+    if act == "relu":
+        ry = np.maximum(ry, 0)
+    args = [dev(x) for x in (A, split, thr, lut, scale, offset)]
+    assert np.array_equal(host(mdn.matmul_act(*args, act=act)), ry)
+    idx = torch.empty((N, C), dtype=torch.uint8, device=DEV)
+    assert np.array_equal(host(mdn.matmul_act(*args, act=act, idx_out=idx)), ry)
+    assert np.array_equal(host(idx), ridx)
+    if act == "none":
+        y, acc, idx = mdn.matmul(*args, want_acc=True, want_idx=True)
+        assert np.array_equal(host(idx), ridx) and np.array_equal(host(acc), racc) and np.array_equal(host(y), ry)
+        assert np.array_equal(host(mdn.matmul(*args)[0]), ry)
+        y = torch.empty((N, M), device=DEV)
+        assert np.array_equal(host(mdn.matmul_noalloc(*args, y_out=y, idx_out=idx)), ry)
+
+
+def test_wide_rows_of_the_row_streaming_kernel(orc):
+    """Its shapes too go in two phases only where the encode has a plan."""
+    N, D, C, M = 98304, 4100, 64, 128
+    A = torch.randn(N, D, device=DEV)
+    rng = np.random.default_rng(9)
+    split = rng.integers(0, D, (C, 4)).astype(np.int32)
+    thr = rng.standard_normal((C, 15), dtype=np.float32)
+    lut, scale, offset = W.random_codes(C, M, seed=9, max_shift=2)
+    y, acc, idx = mdn.matmul(A, *(dev(x) for x in (split, thr, lut, scale, offset)), want_acc=True, want_idx=True)
+    rows = torch.cat([torch.arange(200), torch.arange(49000, 49200), torch.arange(N - 200, N)]).to(DEV)
+    ridx, racc, ry = orc.matmul(host(A[rows]), split, thr, lut, scale, offset)
+    assert np.array_equal(host(idx[rows]), ridx) and np.array_equal(host(acc[rows]), racc)
+    assert np.array_equal(host(y[rows]), ry)
