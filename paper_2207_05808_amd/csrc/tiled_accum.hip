@@ -1181,7 +1181,9 @@ static hipError_t tlaunch(const TArgs& t, int nw, int cus, hipStream_t stream) {
 // reduced across the wavefront, and the row is written once.
 // A copy for every power of two of chunks: 10,000 rows of 100 columns took 7.3
 // us stepping over the 15 chunks they do not have (the whole classifier call 29.0
-// -> 25.8 us, 0.9 of it the one-hot product's prologue).
+// -> 25.8 us, 0.9 of it the one-hot product's prologue).  Each output is divided
+// by the sum, one rounding (as products with the rounded reciprocal, two: 26.1
+// against 26.4 us a call, 58.7 against 59.6 at 1000 columns and 96 codebooks).
 constexpr int kMaxSoftChunks = 16;   // 4-column chunks per lane: M <= 4096
 
 template <int kSoftChunks>
@@ -1209,11 +1211,11 @@ __global__ void __launch_bounds__(256) softmax_rows_kernel(float* y, int64_t N, 
         sum += (v[i].x + v[i].y) + (v[i].z + v[i].w);
       }
     }
-    const float rs = 1.0f / wave_reduce64<false>(sum);   // correctly rounded reciprocal, then products
+    sum = wave_reduce64<false>(sum);
 #pragma unroll
     for (int i = 0; i < kSoftChunks; ++i) {
       const int q = lane + 64 * i;
-      if (q < nq) __builtin_nontemporal_store((tf32x4){v[i].x * rs, v[i].y * rs, v[i].z * rs, v[i].w * rs}, yr + q);
+      if (q < nq) __builtin_nontemporal_store((tf32x4){v[i].x / sum, v[i].y / sum, v[i].z / sum, v[i].w / sum}, yr + q);
     }
   }
 }
