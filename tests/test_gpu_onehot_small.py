@@ -105,3 +105,20 @@ def test_wide_rows_of_the_row_streaming_kernel(orc):
     ridx, racc, ry = orc.matmul(host(A[rows]), split, thr, lut, scale, offset)
     assert np.array_equal(host(idx[rows]), ridx) and np.array_equal(host(acc[rows]), racc)
     assert np.array_equal(host(y[rows]), ry)
+
+
+def test_outputs_past_2_gib(orc):
+    """One column of row groups would hold 2^31 bytes of outputs: two groups
+    per slice, their seam at row 16512."""
+    N, C, M = 33000, 48, 16384
+    lut, scale, offset = W.random_codes(C, M, seed=3, max_shift=8)
+    idx = W.random_indices(N, C, seed=4)
+    didx, args = dev(idx), [dev(x) for x in (lut, scale, offset)]
+    acc, y = mdn.lut_accumulate(didx, *args, want_acc=True)
+    for r0, r1 in ((0, 16000), (16000, N)):   # one group per slice each
+        part, ypart = mdn.lut_accumulate(didx[r0:r1], *args, want_acc=True)
+        assert torch.equal(acc[r0:r1], part) and torch.equal(y[r0:r1], ypart)
+    rows = np.r_[0:20, 16500:16520, N - 20:N]
+    racc, ry = orc.lut_accumulate(idx[rows], lut, scale, offset)
+    at = torch.from_numpy(rows).to(DEV)
+    assert np.array_equal(host(acc[at]), racc) and np.array_equal(host(y[at]), ry)
