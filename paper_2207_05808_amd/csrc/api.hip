@@ -560,24 +560,73 @@ bool macc_shape(const Shape& s) {   // (everything but the index rows' alignment
 }
 bool plan_macc(const Shape& s, MArgs* m, int* blocks_out) {
   if (!macc_shape(s) || !aligned(s.idx_in, 8)) return false;
+  const bool ragged = s.M % 16 != 0;   // output rows are no whole 64-byte pieces
+  const int n64 = (s.M + 63) / 64;
+  const int64_t rows = s.N * (s.y && s.acc ? 2 : 1);   // output rows written
   GArgs g;
   int gng, guq, gnw;
-  if (plan_gfused(s, &g, &gng, &guq, &gnw) && g.vec16) return false;
+  if (plan_gfused(s, &g, &gng, &guq, &gnw)) {
+    if (g.vec16) return false;
+    // The gathers write a row from one wavefront, the slices its parts, lines
+    // that straddle two of them among them: from some size on that costs more
+    // than the gathers do (16 x 196, gathers against the product: 47 / 44 us at
+    // 131,072 rows, 84 / 84 at 262,144, 182 / 217 at 600,000; 16 x 260 37 / 50 at
+    // 65,536, 73 / 76, 121 / 167, 254 / 411; 32 x 132 103 / 70 at 262,144, 209 /
+    // 192 at 600,000, 326 / 361 at 1,048,576).
+    if (ragged && n64 >= 3 && rows * n64 >= (s.C == 16 ? 655360 : s.C == 32 ? 3145728 : INT64_MAX)) return false;
+  }
   const int cp = macc_staged(s.C);
+  const int cus = device_cus();
+  const int64_t tiles64 = (s.N + 63) / 64;
+  auto slices = [&](int w) { return (s.M + w - 1) / w; };
+  auto groups_of = [&](int w) {   // a workgroup per CU
+    int64_t n = cus / slices(w);
+    if (n < 1) n = 1;
+    return n > tiles64 ? tiles64 : n;
+  };
+  auto whole_xcds = [&](int w) {   // ... or up to a quarter fewer, so that the workgroups are a multiple of 8; 0: none
+    const int64_t full = groups_of(w);
+    for (int64_t n = full; 4 * n >= 3 * full; --n)
+      if (n * slices(w) % 8 == 0) return n;
+    return (int64_t)0;
+  };
   // 64 columns per slice, or 32 where then every wavefront still has at most
   // one 64-row tile: half as much to stage, more workgroups.  (32 against 64
   // columns: 64 x 512 outputs 11.3 against 12.8 us at 128 rows, 14.4 against
   // 14.9 at 8192, 18.6 against 18.3 at 16384, 506 against 426 at 1M; 128 x 4096
-  // 22.2 against 22.7 at 1024 rows, 29.8 against 27.5 at 2048.  128 columns, for
-  // C <= 64: 18.2 us at 128 rows, 434 at 1M.)
-  const int cus = device_cus();
-  const int64_t tiles64 = (s.N + 63) / 64;
-  int W = 32, groups = 0;
-  for (;; W = 64) {
-    groups = cus / ((s.M + W - 1) / W);
-    if (groups < 1) groups = 1;
-    if (groups > tiles64) groups = (int)tiles64;
-    if (W == 64 || (tiles64 + groups - 1) / groups <= 8) break;
+  // 22.2 against 22.7 at 1024 rows, 29.8 against 27.5 at 2048.)
+  // 128 columns (C <= 64) only with many rows, and only
+  //  * in ragged rows, where that leaves half as many seams between slices, or
+  //    no multiple of 8 workgroups exists with 64 (below): 64 x 196 128 -> 98 us
+  //    at 262,144 rows (35 / 36 at 65,536), 64 x 700 262 -> 242 at 131,072 (44 /
+  //    45 at 20,000), 16 x 68 149 -> 104 at 1,048,576 (17 / 18 at 131,072).  Not
+  //    where much of a row is then in a last slice that is not whole, whose
+  //    stores are the slow ones: 64 x 1000 1267 / 1318 at 600,000, 16 x 100 154
+  //    / 169 at 1,048,576, but 446 -> 339 at 2,097,152;
+  //  * where the last slice of 64 is three quarters of one, and the first half of
+  //    one of 128: its workgroups are the last to end, and have half of the rows
+  //    then (64 x 432 306 -> 259 us at 600,000 rows, 78 -> 73 at 131,072, but 64 x
+  //    160, half of a slice, 165 / 175 at 1,048,576);
+  //  * for very wide outputs (64 x 4096 480 -> 431 at 131,072 rows, 920 -> 865 at
+  //    262,144; 64 x 2048 equal).
+  auto wide = [&] {
+    if (cp > 64 || n64 < 2) return false;
+    if (ragged) {
+      if (n64 == 2) return (s.M <= 96 && rows >= 524288) || rows * s.M >= 125000000;
+      return s.N * n64 >= 524288 && (n64 <= 4 || (s.M - 1) % 128 < 96) && (n64 % 2 == 0 || !whole_xcds(64));
+    }
+    if (s.M % 64 == 48) return s.C > 32 && n64 % 2 == 1 && s.N >= 131072 && !s.acc;
+    return s.C == 64 && s.M >= 4096 && s.M % 128 == 0 && rows * s.M >= (1ll << 29);
+  };
+  int W = 32;
+  int64_t groups = groups_of(W);
+  if ((tiles64 + groups - 1) / groups > 8) {
+    W = wide() ? 128 : 64;
+    // Ragged rows: neighbouring slices write parts of the same lines, which one
+    // L2 puts together when the slices of a row group run on one XCD, that is
+    // with a multiple of 8 workgroups (64 x 132: 104 -> 77 us at 262,144 rows; 96
+    // x 388 a fifth less from 20,000 rows up).
+    groups = ragged && whole_xcds(W) ? whole_xcds(W) : groups_of(W);
   }
   // A group's outputs stay below 2^31 bytes (32-bit store offsets): whole
   // multiples of the groups above, so that the workgroups still come in rounds
@@ -586,8 +635,8 @@ bool plan_macc(const Shape& s, MArgs* m, int* blocks_out) {
   const int64_t most = ((1ll << 31) - 1) / (4 * (int64_t)s.M) / 64;   // 64-row tiles of a group
   if (most == 0) return false;
   const int64_t rounds = (tiles64 + most * groups - 1) / (most * groups);
-  if (rounds * groups * ((s.M + W - 1) / W) >= (1ll << 31)) return false;
-  groups *= (int)rounds;
+  if (rounds * groups * slices(W) >= (1ll << 31)) return false;
+  groups *= rounds;
   MArgs a{};
   a.idx = s.idx_in; a.lut = static_cast<const int8_t*>(s.lut); a.scale = s.scale; a.offset = s.offset;
   a.y = s.y; a.acc = s.acc; a.col_bias = s.col_bias;
@@ -595,7 +644,7 @@ bool plan_macc(const Shape& s, MArgs* m, int* blocks_out) {
   a.act = s.act == 3 ? 1 : s.act;   // the softmax as a second pass
   a.bias_lds = (a.act != 0 && s.col_bias) ? 1 : 0;
   a.W = W;
-  a.nslices = (s.M + W - 1) / W;
+  a.nslices = slices(W);
   a.xcd_map = (groups * a.nslices) % 8 == 0;
   a.rows_per_group = (tiles64 + groups - 1) / groups * 64;
   int off = cp * W * 16;   // the transposed table slice
@@ -607,7 +656,7 @@ bool plan_macc(const Shape& s, MArgs* m, int* blocks_out) {
   a.lds_total = off;
   if (off > kLdsBytes) return false;
   *m = a;
-  *blocks_out = groups * a.nslices;
+  *blocks_out = (int)(groups * a.nslices);
   return true;
 }
 

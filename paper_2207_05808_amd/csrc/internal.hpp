@@ -174,8 +174,8 @@ hipError_t launch_fenc(const FArgs& f, int blocks, hipStream_t stream);
 
 // Lookup-accumulate as a one-hot int8 product on the matrix cores
 // (onehot_mfma.hip): int8 tables with C % 16 == 0 and C <= 128, M % 4 == 0.
-// Workgroups of 8 wavefronts each own one column slice (macc_width(C)
-// columns) of one row group; with xcd_map (a grid of whole multiples of 8)
+// Workgroups of 8 wavefronts each own one column slice (W columns: 32, 64 or,
+// up to 64 codebooks, 128) of one row group; with xcd_map (a grid of whole multiples of 8)
 // block b takes pair gi = (b % 8) (grid / 8) + b / 8 of the (group, slice)
 // pairs in group-major order, else slice b % nslices of group b / nslices.
 struct MArgs {
@@ -189,7 +189,7 @@ struct MArgs {
   int64_t N, rows_per_group;   // rows_per_group: a multiple of 64
   int C, M, act;          // act: 0 none, 1 bias, 2 bias + ReLU (a softmax runs as a second pass)
   int bias_lds;           // column biases staged in LDS (act != 0 and col_bias given)
-  int W, nslices, xcd_map;   // W: columns per slice (32 or 64)
+  int W, nslices, xcd_map;   // W: columns per slice (32, 64 or 128)
   int off_val, off_sh, off_misc, off_bias, lds_total;   // LDS byte offsets (the table slice at 0)
 };
 constexpr int kMaccGroups = 5;   // one-hot shift groups of 7 for shifts up to 30

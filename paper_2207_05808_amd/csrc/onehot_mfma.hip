@@ -27,7 +27,7 @@
 // LDS once per 64 rows.
 //
 // Layout.  A workgroup (8 wavefronts) owns one column slice of W = 32 WB
-// columns (32 for few rows, else 64) for its lifetime, staged once into LDS transposed, as [codebook]
+// columns (32 for few rows, else 64 or 128) for its lifetime, staged once into LDS transposed, as [codebook]
 // [column][16 prototypes] bytes, so the table operand of a product (32
 // columns x 64 K values) is two 16-byte reads per lane.  Each wavefront takes
 // tiles of 64 rows (two 32-row blocks) of the workgroup's row range
@@ -485,21 +485,24 @@ __global__ void __launch_bounds__(kMWaves * 64) macc_kernel(const MArgs a) {
 
 int macc_staged(int C) { return C <= 64 ? C : C <= 96 ? 96 : 128; }
 
+namespace {
+template <int C16>
+auto macc_of(int W) -> void (*)(MArgs) {
+  if constexpr (C16 <= 4)   // (the table slice fits the LDS)
+    if (W == 128) return macc_kernel<C16, 4>;
+  return W == 64 ? macc_kernel<C16, 2> : macc_kernel<C16, 1>;
+}
+}  // namespace
+
 hipError_t launch_macc(const MArgs& m, int blocks, hipStream_t stream) {
   void (*fn)(MArgs) = nullptr;
-  switch (macc_staged(m.C) / 16 * 2 + (m.W == 64)) {
-    case 2: fn = macc_kernel<1, 1>; break;
-    case 3: fn = macc_kernel<1, 2>; break;
-    case 4: fn = macc_kernel<2, 1>; break;
-    case 5: fn = macc_kernel<2, 2>; break;
-    case 6: fn = macc_kernel<3, 1>; break;
-    case 7: fn = macc_kernel<3, 2>; break;
-    case 8: fn = macc_kernel<4, 1>; break;
-    case 9: fn = macc_kernel<4, 2>; break;
-    case 12: fn = macc_kernel<6, 1>; break;
-    case 13: fn = macc_kernel<6, 2>; break;
-    case 16: fn = macc_kernel<8, 1>; break;
-    default: fn = macc_kernel<8, 2>; break;
+  switch (macc_staged(m.C) / 16) {
+    case 1: fn = macc_of<1>(m.W); break;
+    case 2: fn = macc_of<2>(m.W); break;
+    case 3: fn = macc_of<3>(m.W); break;
+    case 4: fn = macc_of<4>(m.W); break;
+    case 6: fn = macc_of<6>(m.W); break;
+    default: fn = macc_of<8>(m.W); break;
   }
   hipError_t err = hipSuccess;
   launch_prepare(reinterpret_cast<const void*>(fn), kMWaves * 64, m.lds_total, &err);

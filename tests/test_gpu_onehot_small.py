@@ -122,3 +122,23 @@ def test_outputs_past_2_gib(orc):
     racc, ry = orc.lut_accumulate(idx[rows], lut, scale, offset)
     at = torch.from_numpy(rows).to(DEV)
     assert np.array_equal(host(acc[at]), racc) and np.array_equal(host(y[at]), ry)
+
+
+@pytest.mark.parametrize("N,C,M", [(131100, 16, 260), (140000, 32, 196), (263000, 48, 132), (131073, 64, 304),
+                                   (90000, 64, 452), (60000, 48, 700), (131080, 64, 4096)])
+def test_slices_of_128_columns(orc, N, C, M):
+    """Many rows: the slices and groups of ragged rows, the last slice of three
+    quarters, very wide outputs (and 16 codebooks' gathers), against the same
+    rows in small calls, and a few of them against the oracle."""
+    lut, scale, offset = W.random_codes(C, M, seed=M, max_shift=8)
+    idx = W.random_indices(N, C, seed=C)
+    didx, args = dev(idx), [dev(x) for x in (lut, scale, offset)]
+    _, y = mdn.lut_accumulate(didx, *args)
+    for r0 in range(0, N, 16000):
+        assert torch.equal(y[r0:r0 + 16000], mdn.lut_accumulate(didx[r0:r0 + 16000], *args)[1])
+    acc, y2 = mdn.lut_accumulate(didx, *args, want_acc=True)
+    assert torch.equal(y, y2)
+    rows = np.r_[0:9, N // 2:N // 2 + 9, N - 9:N]
+    racc, ry = orc.lut_accumulate(idx[rows], lut, scale, offset)
+    at = torch.from_numpy(rows).to(DEV)
+    assert np.array_equal(host(acc[at]), racc) and np.array_equal(host(y[at]), ry)

@@ -83,6 +83,11 @@ def api(tmp_path_factory):
 FAKE = ctypes.c_void_p(0x1000)
 
 
+def fits_gathers(C, M):
+    """Tables the gather-fused kernel takes (C divides 64, 16-bit entries in 160 KB of LDS beside its offsets)."""
+    return 64 % C == 0 and 2 * (16 * C + 1) * (M + 7 & ~7) < 150_000
+
+
 def accumulate(L, N, C, M):
     assert L.maddness_lut_accumulate(FAKE, N, C, FAKE, FAKE, FAKE, M, None, FAKE, None) == 0
     return L.routes().decode().split("\n")[:-1]
@@ -92,7 +97,7 @@ def check_split(route, N, M):
     """The one-hot product's split covers every row and column, in groups whose outputs stay below 2^31 bytes."""
     name, W, nslices, rows, blocks, xcd = route.split()
     W, nslices, rows, blocks, xcd = int(W), int(nslices), int(rows), int(blocks), int(xcd)
-    assert name == "macc" and W in (32, 64) and nslices == -(-M // W)
+    assert name == "macc" and W in (32, 64, 128) and nslices == -(-M // W)
     groups = blocks // nslices
     assert blocks == groups * nslices and rows % 64 == 0
     assert groups * rows >= N and (rows - 64) * groups < N + 64 * groups
@@ -108,8 +113,36 @@ def test_one_hot_product_at_any_output_size(api, N, C, M):
     """Large outputs keep the one-hot product; they take more row groups."""
     (route,) = accumulate(api, N, C, M)
     W, groups = check_split(route, N, M)
-    per_round = max(1, 256 // -(-M // W))
-    assert groups % min(per_round, -(-N // 64)) == 0
+    # whole rounds of (almost) a workgroup per compute unit
+    slices = -(-M // W)
+    full = min(max(1, 256 // slices), -(-N // 64))
+    assert any(groups % g == 0 for g in range(-(-3 * full // 4), full + 1))
+
+
+def test_one_hot_product_of_ragged_rows(api):
+    """Output rows that are no whole 64-byte pieces: a multiple of 8 workgroups
+    wherever that costs at most a quarter of them, so that the slices of a row
+    group run on one XCD; 128 columns only for up to 64 codebooks and many rows."""
+    for C in (32, 48, 64, 96, 128):
+        for M in range(132, 3000, 52):
+            for N in (40000, 131072, 700000):
+                (route,) = accumulate(api, N, C, M)
+                W, groups = check_split(route, N, M)
+                slices = -(-M // W)
+                assert W == 64 or (W == 128 and C <= 64 and N * -(-M // 64) >= 524288)
+                full = 256 // slices
+                if M % 16 and any(g * slices % 8 == 0 for g in range(-(-3 * full // 4), full + 1)):
+                    assert groups * slices % 8 == 0
+                assert 4 * groups >= 3 * full
+
+
+def test_few_codebooks_and_many_ragged_rows_gather(api):
+    for C, M, N, gathers in ((16, 196, 163839, False), (16, 196, 163840, True), (16, 128, 1 << 20, True),
+                             (16, 100, 1 << 22, False), (16, 208, 4096, True), (16, 1000, 1 << 20, False),
+                             (32, 132, (1 << 20) - 1, False), (32, 132, 1 << 20, True), (32, 196, 1 << 20, False),
+                             (64, 132, 1 << 20, False)):
+        (route,) = accumulate(api, N, C, M)
+        assert route.startswith("gfused") == gathers
 
 
 def test_one_hot_product_split(api):
@@ -120,7 +153,7 @@ def test_one_hot_product_split(api):
         N = int(2 ** rng.uniform(0, 24))
         route = accumulate(api, N, C, M)
         if route[0].startswith("gfused"):
-            assert M % 16 == 0 and 64 % C == 0
+            assert fits_gathers(C, M) and (M % 16 == 0 or (M > 128 and N >= 131072))
             continue
         assert len(route) == 1
         check_split(route[0], N, M)
