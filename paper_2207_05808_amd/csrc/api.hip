@@ -752,36 +752,66 @@ int two_phase(const Shape& s, uint8_t* idx, hipStream_t stream) {
 // Whether a fused call that could run as one launch runs faster as encode +
 // the one-hot product, through an index array.  Not for a row softmax, which
 // the single-launch kernels fuse and the two-phase path runs as a pass of its
-// own.
-//  * The row-streaming kernel's shapes, from kTwoPhaseMinCols columns: on 1M
-//    rows of 512 columns of A with 64 codebooks, 0.84 against 1.05 ms at 512
-//    output columns, 0.62 against 0.94 at 256, 0.51 against 0.89 at 128 (the
-//    encode alone is 0.37 ms).
-//  * The general kernel's, and the gather-fused kernel's where it would stage
-//    the table element by element, from kTwoPhaseMinTable entries per prototype
-//    (C M): 64 x 100 outputs 17 against 22 us at 300 rows, 29 against 64 at
-//    30000, 80 against 204 at 131072; 48 x 100 16 / 25 / 69 against 19 / 61 /
-//    202; 32 x 100 12 against 14 at 300 rows.  Below (64 x 20: about 15 against
-//    13 us at 300 rows) the second launch costs more than it gains.
-// Only where the encode has a plan: it stages whole rows of A (D up to 4096 in
-// 16-byte units, else up to about 10,000), which the single launches need not.
+// own; only where the encode has a plan: it stages whole rows of A (D up to
+// 4096 in 16-byte units, else up to about 10,000), which the single launches
+// need not.  Rows that are not whole 16-byte units it stages a word at a time,
+// several times slower, so those are judged apart.  In us, one launch / two:
+//  * The row-streaming kernel's shapes, from kTwoPhaseMinCols columns and rows in
+//    16-byte units: on 1M rows of 512 columns of A with 64 codebooks, 1050 / 840
+//    at 512 output columns, 940 / 620 at 256, 890 / 510 at 128 (the encode alone
+//    is 370); rows of 513 171 / 234 at 131,072 rows, 64 x 128.
+//  * Against the general kernel (no layer output), from kTwoPhaseMinTable entries
+//    per prototype (C M): 64 x 100 outputs 22 / 17 at 300 rows, 64 / 29 at 30,000,
+//    204 / 80 at 131,072; 48 x 100 19 / 16, 61 / 25, 202 / 69.  Below (64 x 20:
+//    about 13 / 15 at 300 rows) the second launch costs more than it gains.
+//    Rows not in 16-byte units: from 8192 rows (32 x 100, D 577: 15 / 20 at 1024
+//    rows, 19 / 20 at 4096, 24 / 21 at 8192, 75 / 62 at 32,768), less where both
+//    stage long rows alike; before that for larger tables with D below 768 (64 x
+//    72, D 577 29 / 24 at 4096; D 1025 32 / 48) and shorter rows (16 x 200, D 129
+//    19 / 13 at 4096; 48 x 64, D 193 15 / 16).  Not 16 codebooks' narrow tables
+//    with rows of about 1000 (16 x 200, D 1025: 68 / 84 at 16,384).
+//  * Against the gather-fused kernel where it would stage the table element by
+//    element (a fixed 18 to 31 us) and does not read rows of A whole.  16-byte
+//    rows: while the encode's reading is short (16 x 200 18 / 10 at 64 rows, 24 /
+//    17 at 32,768, 44 / 48 at 131,072; D 2304 20 / 15 at 4096, 30 / 33 at 16,384;
+//    32 x 100, D 4096 22 / 22 at 4096, 41 / 54 at 16,384), for more codebooks also
+//    beyond, except narrow tables with many short rows (32 x 100, D 128 75 / 84
+//    at 300,000; 32 x 132 128 / 108; 64 x 60 120 / 91).  Other rows: 32 x 100, D
+//    257 22 / 18 at 16,384 rows, 46 / 83 at 131,072, D 577 18 / 19 at 64, 75 / 311
+//    at 131,072; 64 x 72, D 577 35 / 27 at 8192, D 1025 32 / 30 at 1024, 34 / 48 at
+//    4096.
 constexpr int kTwoPhaseMinCols = 128, kTwoPhaseMinTable = 3072;
 bool two_phase_faster(const Shape& s) {
   if (s.act == 3 || !macc_shape(s)) return false;
-  FArgs f;
-  int blocks;
-  if (plan_fenc(s, &f, &blocks, nullptr, 0)) {
-    if (s.M < kTwoPhaseMinCols) return false;
-  } else {
-    GArgs g;
-    int ng, uq, nw;
-    if (plan_gfused(s, &g, &ng, &uq, &nw) && g.vec16) return false;
-    if (s.C * s.M < kTwoPhaseMinTable) return false;
-  }
   Shape e = s;
   e.mode = kEncode;
   Plan p;
-  return plan(e, &p, false) == MADDNESS_OK;
+  if (plan(e, &p, false) != MADDNESS_OK) return false;
+  const bool units = p.a.vec_rows != 0;   // rows of A in 16-byte units
+  FArgs f;
+  int blocks;
+  if (plan_fenc(s, &f, &blocks, nullptr, 0)) return units && s.M >= kTwoPhaseMinCols;
+  GArgs g;
+  int ng, uq, nw;
+  const bool gathers = plan_gfused(s, &g, &ng, &uq, &nw);
+  const int table = s.C * s.M;
+  if (gathers && g.vec16) return false;
+  if (table < kTwoPhaseMinTable) return false;
+  const int64_t read = s.N * s.D;
+  if (s.act == 0 && plan(s, &p, true) == MADDNESS_OK) {
+    if (units) return true;
+    if (s.C == 16 && s.M < 256 && s.D >= 768 && s.D < 2048) return false;
+    if (s.N >= (s.D < 2048 ? 8192 : 4096)) return true;
+    return s.D < 768 && (table >= 4096 || s.D <= 160 || s.C >= 96 || (s.C <= 32 && s.D < 512 && s.N >= 4096));
+  }
+  if (!gathers) return true;
+  if (units) {
+    if (s.N < 65536 && read < (1 << 25)) return true;
+    return s.C > 16 && s.D < 3072 && (table >= 4096 || s.C >= 64 || s.N < 131072 || s.D >= 512);
+  }
+  if (s.D < 512) return s.N <= 32768 && read < (table >= 4096 && s.C > 16 ? 1 << 24 : 1 << 23);
+  if (table >= 4096) return s.D < 2400 && s.N <= (s.D < 768 ? 8192 : 1024);
+  return s.C == 16 && s.D < 768 && s.N <= 4096;
 }
 
 // Whether a fused call runs as one launch (the gather-fused kernel, or the

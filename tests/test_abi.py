@@ -125,9 +125,9 @@ def test_matmul_index_bytes_of_rows_the_encode_cannot_stage(L):
     Q = L.maddness_matmul_index_bytes
     for C, M in ((32, 100), (64, 72)):
         for act in (0, 2):
-            for D in (576, 4096, 4101):
+            for D in (576, 4096):
                 assert Q(FAKE, 1000, D, D, C, M, 0, act) == 1000 * C
-            for D in (4100, 4608, 10300, 10301):
+            for D in (4100, 4101, 4608, 10300, 10301):
                 assert Q(FAKE, 1000, D, D, C, M, 0, act) == 0
     for D, n in ((4096, 98304 * 64), (4100, 0), (4608, 0)):   # the row-streaming kernel's shapes
         assert Q(FAKE, 98304, D, D, 64, 512, 0, 0) == n

@@ -169,3 +169,38 @@ def test_two_phases_where_the_encode_has_a_plan(api, D, two, act):
                                        None) == 0
         route = api.routes().decode().split("\n")[:-1]
         assert [r.split()[0] for r in route] == (["encode", "macc"] if two else ["gfused"])
+
+
+def route(L, N, D, C, M, act, lda=None):
+    n = L.maddness_matmul_index_bytes(FAKE, N, D, lda or D, C, M, 0, act)
+    assert L.maddness_matmul_act(FAKE, N, D, lda or D, FAKE, FAKE, C, FAKE, FAKE, FAKE, M, None, act, FAKE,
+                                 FAKE if n > 0 else None, None) == 0
+    return "+".join(r.split()[0] for r in L.routes().decode().split("\n")[:-1])
+
+
+@pytest.mark.parametrize("N,D,C,M,act,want", [
+    # rows of A in 16-byte units: two phases against the general kernel, and
+    # against the gathers while the encode has little to read or for many codebooks
+    (64, 576, 32, 100, 0, "encode+macc"), (300000, 576, 32, 100, 0, "encode+macc"), (64, 576, 64, 40, 0, "fused"),
+    (32768, 128, 16, 200, 2, "encode+macc"), (131072, 128, 16, 200, 2, "gfused"), (16384, 2304, 16, 200, 2, "gfused"),
+    (300000, 1024, 32, 132, 2, "encode+macc"), (131072, 128, 32, 100, 2, "gfused"), (131072, 256, 64, 60, 2, "encode+macc"),
+    (16384, 4096, 32, 132, 2, "gfused"), (4096, 4096, 32, 100, 2, "encode+macc"),
+    # rows that are not
+    (1024, 577, 32, 100, 0, "fused"), (8192, 577, 32, 100, 0, "encode+macc"), (1024, 577, 64, 72, 0, "encode+macc"),
+    (1024, 1025, 64, 72, 0, "fused"), (1024, 257, 32, 100, 0, "fused"), (4096, 257, 32, 100, 0, "encode+macc"),
+    (1000, 4101, 64, 72, 2, "gfused"), (4096, 129, 16, 200, 0, "encode+macc"), (100000, 1025, 16, 200, 0, "fused"),
+    (131072, 577, 32, 100, 2, "gfused"), (131072, 577, 16, 200, 2, "gfused"), (1000, 257, 32, 100, 2, "encode+macc"),
+    (131072, 129, 16, 200, 2, "gfused"), (8192, 577, 64, 72, 2, "encode+macc"), (4096, 1025, 64, 72, 2, "gfused"),
+    # the row-streaming kernel's shapes
+    (131072, 512, 64, 128, 0, "encode+macc"), (131072, 513, 64, 128, 0, "fenc+trow-wide"),
+    (131072, 512, 64, 112, 2, "fenc+trow-wide"),
+    # no single launch
+    (131072, 577, 64, 100, 2, "encode+macc"), (64, 1025, 48, 64, 2, "encode+macc")])
+def test_fused_routes(api, N, D, C, M, act, want):
+    assert route(api, N, D, C, M, act) == want
+
+
+def test_row_stride_counts_as_alignment(api):
+    assert route(api, 131072, 576, 32, 100, 2) == "encode+macc"
+    assert route(api, 131072, 576, 32, 100, 2, lda=577) == "gfused"
+    assert route(api, 1024, 576, 32, 100, 0, lda=578) == "fused"
