@@ -575,6 +575,17 @@ bool plan_macc(const Shape& s, MArgs* m, int* blocks_out) {
     // 192 at 600,000, 326 / 361 at 1,048,576).
     if (ragged && n64 >= 3 && rows * n64 >= (s.C == 16 ? 655360 : s.C == 32 ? 3145728 : INT64_MAX)) return false;
   }
+  // A row softmax is a second pass here.  Large outputs of few codebooks go
+  // through the kernels that fuse it where a row is one of their column tiles,
+  // in 16-byte units: the row-uniform kernel's (16 x 512 51 / 33 us at 16,384
+  // rows, fused / here, 53 / 63 at 49,152, 99 / 159 at 131,072; 32 x 512 69 / 70 at
+  // 49,152, 134 / 173; 48 x 512 162 / 143 at 98,304) and up to 64 columns the
+  // column-tiled kernel's (48 x 64 35 / 31 at 32,768, 44 / 50 at 65,536, 73 / 87 at
+  // 131,072; 80 x 64 65 / 67, 112 / 119; 96 x 64 127 / 129, 237 / 243 at 262,144).
+  if (s.act == 3 && s.M % 16 == 0 && aligned(s.lut, 16)) {
+    if (s.M == kRowTileCols && s.C < 48 && s.N >= 49152) return false;
+    if (s.M <= 64 && s.C <= 80 && s.N >= 1365 * (int64_t)s.C) return false;
+  }
   const int cp = macc_staged(s.C);
   const int cus = device_cus();
   const int64_t tiles64 = (s.N + 63) / 64;

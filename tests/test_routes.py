@@ -194,6 +194,12 @@ def route(L, N, D, C, M, act, lda=None):
     # the row-streaming kernel's shapes
     (131072, 512, 64, 128, 0, "encode+macc"), (131072, 513, 64, 128, 0, "fenc+trow-wide"),
     (131072, 512, 64, 112, 2, "fenc+trow-wide"),
+    # a row softmax: large outputs of few codebooks in a kernel that fuses it
+    (48000, 128, 16, 512, 3, "encode+macc+softmax"), (49152, 128, 16, 512, 3, "encode+trow"),
+    (131072, 256, 32, 512, 3, "encode+trow"), (131072, 384, 48, 512, 3, "encode+macc+softmax"),
+    (65000, 384, 48, 64, 3, "encode+macc+softmax"), (65536, 384, 48, 64, 3, "encode+tacc"),
+    (131072, 640, 80, 32, 3, "encode+tacc"), (131072, 384, 48, 100, 3, "encode+macc+softmax"),
+    (131072, 768, 96, 64, 3, "encode+macc+softmax"), (1 << 20, 384, 48, 128, 3, "encode+macc+softmax"),
     # no single launch
     (131072, 577, 64, 100, 2, "encode+macc"), (64, 1025, 48, 64, 2, "encode+macc")])
 def test_fused_routes(api, N, D, C, M, act, want):
