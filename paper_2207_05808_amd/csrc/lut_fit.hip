@@ -341,6 +341,41 @@ __device__ __forceinline__ void scatter_bucket(const int32_t* __restrict__ perm,
   if (lane < TC && m < M) done((int64_t)c * kK + k, m, acc);
 }
 
+// The same sums for small buckets, a wavefront per (codebook, bucket, 64
+// columns): 16 rows' loads together, no LDS, so that many buckets are in flight
+// where a workgroup each would spend its time on starting and ending.
+constexpr int kFewWaves = 4;
+template <class V, class F>
+__device__ __forceinline__ void scatter_few_rows(const int32_t* __restrict__ perm, const int32_t* __restrict__ start,
+                                                 int64_t N, int C, const V* __restrict__ Y, int M, F&& done) {
+  constexpr int kU = 16;
+  const int lane = threadIdx.x & 63;
+  const int ntile = (M + 63) / 64;
+  const int64_t w = (int64_t)blockIdx.x * kFewWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (w >= (int64_t)C * kK * ntile) return;   // uniform
+  const int64_t r = w / ntile;   // bucket 16 c + k
+  const int c = (int)(r / kK), k = (int)(r % kK);
+  const int m = (int)(w % ntile) * 64 + lane;
+  const V* yc = Y + min(m, M - 1);   // columns past M read column M - 1
+  const int32_t* pc = perm + (int64_t)c * (N + kPermPad);
+  const int64_t p0 = start[c * (kK + 1) + k], p1 = start[c * (kK + 1) + k + 1];
+  double acc = 0.0;
+  for (int64_t p = p0; p < p1; p += 64) {
+    const int cnt = (int)min((int64_t)64, p1 - p);
+    const int numbers = pc[min(p + lane, p1 - 1)];   // one row number per lane
+    for (int j = 0; j < cnt; j += kU) {
+      V v[kU];
+#pragma unroll
+      for (int u = 0; u < kU; ++u)
+        v[u] = yc[(int64_t)__builtin_amdgcn_readlane(numbers, min(j + u, cnt - 1)) * M];
+      // (rows past the bucket add +0: the sum starts at +0 and is never -0)
+#pragma unroll
+      for (int u = 0; u < kU; ++u) acc = __dadd_rn(acc, j + u < cnt ? (double)v[u] : 0.0);
+    }
+  }
+  if (m < M) done(r, m, acc);
+}
+
 constexpr int kScCols = 64;                                            // columns of floats per workgroup
 // of doubles: at most 8 tiles of 16 for narrow layers (their chains are what
 // counts: 79 us against 86 with 32 columns, C 32, M 64), else 64 (the LDS is what
@@ -348,25 +383,55 @@ constexpr int kScCols = 64;                                            // column
 // a step against 6.9 with 32 columns)
 constexpr int step_cols(int M) { return M <= 128 ? 16 : 64; }
 unsigned scatter_grid(int C, int M, int cols) { return (unsigned)(C * kK * ((M + cols - 1) / cols)); }
+unsigned few_rows_grid(int C, int M) {
+  return (unsigned)(((int64_t)C * kK * ((M + 63) / 64) + kFewWaves - 1) / kFewWaves);
+}
+// Where a wavefront per bucket is the faster one, also when one bucket holds
+// half of the rows (us, with random trees' buckets, a workgroup / a wavefront
+// each): the sums 64 codebooks x 512 columns 53 / 31 at 500 rows, 56 / 52 at 1000,
+// 61 / 96 at 2000, 256 x 1024 347 / 104, 370 / 185; three gradient steps of 256
+// x 128 916 / 219 at 500 rows, 1028 / 501 at 2000, 1305 / 930 at 4096, of 128 x
+// 10 111 / 83, 121 / 145, 150 / 247, and of 128 x 512 1011 / 545, 1093 / 1202.
+bool few_rows_sum(int64_t N, int C, int M) { return N <= 1024 && scatter_grid(C, M, kScCols) >= 8 * N; }
+bool few_rows_step(int64_t N, int C, int M) {
+  return N <= (step_cols(M) == 16 ? 8192 : 1024) && scatter_grid(C, M, step_cols(M)) >= 4 * N;
+}
 
 __global__ void __launch_bounds__(kScWaves * 64)
 scatter_kernel(const int32_t* __restrict__ perm, const int32_t* __restrict__ start, int64_t N, int C,
                const float* __restrict__ Y, int M, double* __restrict__ R) {
   scatter_bucket<float, kScCols>(perm, start, N, C, Y, M, [&](int64_t r, int m, double v) { R[r * M + m] = v; });
 }
+__global__ void __launch_bounds__(kFewWaves * 64)
+scatter_few_kernel(const int32_t* __restrict__ perm, const int32_t* __restrict__ start, int64_t N, int C,
+                   const float* __restrict__ Y, int M, double* __restrict__ R) {
+  scatter_few_rows<float>(perm, start, N, C, Y, M, [&](int64_t r, int m, double v) { R[r * M + m] = v; });
+}
 
 // The gradient step on the sums just made: T = T - eta (R + 2 lambda (T - T0))
+struct GradStep {
+  const float* T0;
+  double two_lam, eta;
+  double* T;
+  int M;
+  __device__ void operator()(int64_t r, int m, double v) const {
+    const int64_t e = r * M + m;
+    const double g = __dadd_rn(v, __dmul_rn(two_lam, __dsub_rn(T[e], (double)T0[e])));
+    T[e] = __dsub_rn(T[e], __dmul_rn(eta, g));
+  }
+};
 template <int TC>
 __global__ void __launch_bounds__(kScWaves * 64)
 scatter_step_kernel(const int32_t* __restrict__ perm, const int32_t* __restrict__ start, int64_t N, int C,
                     const double* __restrict__ Dv, int M, const float* __restrict__ T0, double lam, double eta,
                     double* __restrict__ T) {
-  const double two_lam = __dmul_rn(2.0, lam);
-  scatter_bucket<double, TC>(perm, start, N, C, Dv, M, [&](int64_t r, int m, double v) {
-    const int64_t e = r * M + m;
-    const double g = __dadd_rn(v, __dmul_rn(two_lam, __dsub_rn(T[e], (double)T0[e])));
-    T[e] = __dsub_rn(T[e], __dmul_rn(eta, g));
-  });
+  scatter_bucket<double, TC>(perm, start, N, C, Dv, M, GradStep{T0, __dmul_rn(2.0, lam), eta, T, M});
+}
+__global__ void __launch_bounds__(kFewWaves * 64)
+scatter_few_step_kernel(const int32_t* __restrict__ perm, const int32_t* __restrict__ start, int64_t N, int C,
+                        const double* __restrict__ Dv, int M, const float* __restrict__ T0, double lam, double eta,
+                        double* __restrict__ T) {
+  scatter_few_rows<double>(perm, start, N, C, Dv, M, GradStep{T0, __dmul_rn(2.0, lam), eta, T, M});
 }
 
 // -------------------------------------------------------------- assemble
@@ -857,8 +922,12 @@ hipError_t launch_scatter(const uint8_t* idx, int64_t N, int C, const float* Y, 
                           int32_t* perm, int32_t* start, hipStream_t stream) {
   hipError_t e = launch_partition(idx, N, C, perm, start, stream);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(scatter_kernel, dim3(scatter_grid(C, M, kScCols)), dim3(kScWaves * 64), 0, stream, perm, start, N,
-                     C, Y, M, R);
+  if (few_rows_sum(N, C, M))
+    hipLaunchKernelGGL(scatter_few_kernel, dim3(few_rows_grid(C, M)), dim3(kFewWaves * 64), 0, stream, perm, start, N,
+                       C, Y, M, R);
+  else
+    hipLaunchKernelGGL(scatter_kernel, dim3(scatter_grid(C, M, kScCols)), dim3(kScWaves * 64), 0, stream, perm, start,
+                       N, C, Y, M, R);
   return hipGetLastError();
 }
 
@@ -928,9 +997,11 @@ hipError_t launch_fit_gd(const uint8_t* idx, int64_t N, int C, const float* Y, i
       hipLaunchKernelGGL(resid, dim3(rows), dim3(256), 0, stream, idx, N, C, T, M, bias, act, P, D);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    auto step = step_cols(M) == 16 ? scatter_step_kernel<16> : scatter_step_kernel<64>;
-    hipLaunchKernelGGL(step, dim3(scatter_grid(C, M, step_cols(M))), dim3(kScWaves * 64), 0, stream, perm,
-                       start, N, C, D, M, T0, lam, eta, T);
+    const bool few = few_rows_step(N, C, M);
+    auto step = few ? scatter_few_step_kernel : step_cols(M) == 16 ? scatter_step_kernel<16> : scatter_step_kernel<64>;
+    const unsigned blocks = few ? few_rows_grid(C, M) : scatter_grid(C, M, step_cols(M));
+    hipLaunchKernelGGL(step, dim3(blocks), dim3((few ? kFewWaves : kScWaves) * 64), 0, stream, perm, start, N, C, D, M,
+                       T0, lam, eta, T);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
