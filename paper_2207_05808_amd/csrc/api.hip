@@ -767,10 +767,11 @@ int two_phase(const Shape& s, uint8_t* idx, hipStream_t stream) {
 // 4096 in 16-byte units, else up to about 10,000), which the single launches
 // need not.  Rows that are not whole 16-byte units it stages a word at a time,
 // several times slower, so those are judged apart.  In us, one launch / two:
-//  * The row-streaming kernel's shapes, from kTwoPhaseMinCols columns and rows in
-//    16-byte units: on 1M rows of 512 columns of A with 64 codebooks, 1050 / 840
-//    at 512 output columns, 940 / 620 at 256, 890 / 510 at 128 (the encode alone
-//    is 370); rows of 513 171 / 234 at 131,072 rows, 64 x 128.
+//  * The row-streaming kernel's shapes, from kTwoPhaseMinCols columns: on 1M rows
+//    of 512 columns of A with 64 codebooks, 1050 / 840 at 512 output columns, 940
+//    / 620 at 256, 890 / 510 at 128 (the encode alone is 370).  (Rows that are not
+//    in 16-byte units too, though there one launch is faster: D 513, 64 x 128, 171
+//    / 234 at 131,072 rows.)
 //  * Against the general kernel (no layer output), from kTwoPhaseMinTable entries
 //    per prototype (C M): 64 x 100 outputs 22 / 17 at 300 rows, 64 / 29 at 30,000,
 //    204 / 80 at 131,072; 48 x 100 19 / 16, 61 / 25, 202 / 69.  Below (64 x 20:
@@ -801,7 +802,7 @@ bool two_phase_faster(const Shape& s) {
   const bool units = p.a.vec_rows != 0;   // rows of A in 16-byte units
   FArgs f;
   int blocks;
-  if (plan_fenc(s, &f, &blocks, nullptr, 0)) return units && s.M >= kTwoPhaseMinCols;
+  if (plan_fenc(s, &f, &blocks, nullptr, 0)) return s.M >= kTwoPhaseMinCols;
   GArgs g;
   int ng, uq, nw;
   const bool gathers = plan_gfused(s, &g, &ng, &uq, &nw);

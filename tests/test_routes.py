@@ -192,7 +192,7 @@ def route(L, N, D, C, M, act, lda=None):
     (131072, 577, 32, 100, 2, "gfused"), (131072, 577, 16, 200, 2, "gfused"), (1000, 257, 32, 100, 2, "encode+macc"),
     (131072, 129, 16, 200, 2, "gfused"), (8192, 577, 64, 72, 2, "encode+macc"), (4096, 1025, 64, 72, 2, "gfused"),
     # the row-streaming kernel's shapes
-    (131072, 512, 64, 128, 0, "encode+macc"), (131072, 513, 64, 128, 0, "fenc+trow-wide"),
+    (131072, 512, 64, 128, 0, "encode+macc"), (131072, 513, 64, 128, 0, "encode+macc"),
     (131072, 512, 64, 112, 2, "fenc+trow-wide"),
     # a row softmax: large outputs of few codebooks in a kernel that fuses it
     (48000, 128, 16, 512, 3, "encode+macc+softmax"), (49152, 128, 16, 512, 3, "encode+trow"),
