@@ -13,10 +13,10 @@
 //   q          = round-half-even((T - o_c) * 2^-e_c),  |q| <= 127.
 // T = P B takes four launches: the range of every (codebook, column tile),
 // parked in the tile's own part of the codes; per codebook the offset and the
-// exponent (parked in scale_out as an integer); the codes; the scales.  The
-// entries are evaluated in the first and the third (no workspace for a double
-// copy of T).  A given table T takes three: statistics (one workgroup per
-// codebook), codes, scales.
+// exponent (parked in scale_out as an integer); the codes; the scales.  (Three
+// for small tables: range and exponent in one.)  The entries are evaluated in
+// the first and the third (no workspace for a double copy of T).  A given table
+// T takes three: statistics (one workgroup per codebook), codes, scales.
 //
 // Zero prototype columns.  P[c] is zero outside codebook c's subspace, so most
 // terms are a zero times a finite weight.  A sum that starts at +0 is never
@@ -25,13 +25,16 @@
 // B[d][m] is finite (0 * inf and 0 * NaN are NaN).  Each workgroup lists the
 // columns of its codebook that are not all zero, ascending, and the weights
 // are checked on the way: every (codebook, tile) checks its share of B's rows.
-// One non-finite weight anywhere, and every column is taken.
+// One non-finite weight anywhere, and every column is taken (for the fp32 table,
+// whose columns do not depend on each other, by the tiles that hold one).
 //
 // Bound: launches and latency (P and B once from HBM, a few columns per
 // codebook); with prototypes that have no zero column, the fp64 FMA rate.
-// 128 codebooks, D 1024, M 4096 (8 nonzero columns per codebook): 57 us a build
+// 128 codebooks, D 1024, M 4096 (8 nonzero columns per codebook): 50 us a build
 // against 14.2 ms with every column taken and one workgroup per codebook.
 #include "internal.hpp"
+
+#include <type_traits>
 
 namespace mdn {
 
@@ -43,6 +46,7 @@ constexpr int kStatsThreads = 1024;
 constexpr int kStatsILP = 4;
 
 constexpr int kChunk = 512;   // prototype columns listed at a time
+constexpr int kAllColumns = 4;   // up to so many are all taken: the weights need no look then
 
 // What a workgroup of kBuildThreads keeps of one chunk of P[c]: the columns
 // that are not all zero, ascending, and their 16 values (as doubles: they are
@@ -51,29 +55,48 @@ struct TileLds {
   double p[kChunk][kK];
   int d[kChunk];
   int cnt[2 * kBuildThreads / 64];
+  int each[kBuildThreads / 64];   // whether a wavefront takes every column
 };
 
-// The 16 x (CPT kBuildThreads) tile of T from column col0 of codebook c: this
-// thread's columns are colof(j), t[k][j] their sums over d ascending.  The
-// product of two floats is exact in double, so the fused multiply-add rounds
-// exactly as a multiply and an add do.  `dense` takes the zero columns too.
-// Columns past M read column M - 1.
-template <int CPT, bool VEC>
+// A tile of T from column col0 of codebook c, all 16 prototypes: a thread has
+// KPT of them from k0() and CPT columns colof(j), t[k][j] their sums over d
+// ascending.  The product of two floats is exact in double, so the fused
+// multiply-add rounds exactly as a multiply and an add do.  `dense` takes the
+// zero columns too.  Columns past M read column M - 1.
+template <int CPT, bool VEC, int KPT>
 struct Tile {
-  static constexpr int kCpt = CPT;
+  static constexpr int kCpt = CPT, kKpt = KPT;
   static constexpr bool kVec = VEC;
-  static constexpr int kCols = CPT * kBuildThreads;
+  static constexpr int kAcross = kBuildThreads * KPT / kK;   // threads side by side
+  static constexpr int kCols = CPT * kAcross;
+  static __device__ __forceinline__ int k0() { return (int)threadIdx.x / kAcross * KPT; }
   static __device__ __forceinline__ int colof(int col0, int j) {
-    return VEC ? col0 + CPT * (int)threadIdx.x + j : col0 + (int)threadIdx.x + j * kBuildThreads;
+    const int x = (int)threadIdx.x % kAcross;
+    return VEC ? col0 + CPT * x + j : col0 + x + j * kAcross;
   }
+  // whether a weight of rows d0 .. d1 in the tile's columns, as far as this
+  // thread looks (the threads of a column share its rows), is not finite
+  static __device__ __forceinline__ bool not_finite(const float* __restrict__ B, int64_t d0, int64_t d1, int M,
+                                                    int col0) {
+    bool bad = false;
+#pragma unroll 8
+    for (int64_t d = d0 + threadIdx.x / kAcross; d < d1; d += kK / KPT)
+#pragma unroll
+      for (int j = 0; j < CPT; ++j) bad |= !__builtin_isfinite(B[d * M + min(colof(col0, j), M - 1)]);
+    return bad;
+  }
+  // EACH: `dense` differs between threads, and one is enough (asked of all of
+  // them once the first prototypes have been requested).
+  template <bool EACH = false>
   static __device__ void sums(const float* __restrict__ P, const float* __restrict__ B, int D, int M, int c, int col0,
-                              bool dense, TileLds& s, double (&t)[kK][CPT]) {
+                              bool dense, TileLds& s, double (&t)[KPT][CPT]) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int NW = kBuildThreads / 64;
 #pragma unroll
-    for (int k = 0; k < kK; ++k)
+    for (int k = 0; k < KPT; ++k)
 #pragma unroll
       for (int j = 0; j < CPT; ++j) t[k][j] = 0.0;
+    const int kt = k0();
     const float* pc = P + (int64_t)c * kK * D;
     const float* b[CPT];
 #pragma unroll
@@ -89,7 +112,15 @@ struct Tile {
 #pragma unroll
         for (int k = 0; k < kK; ++k) v[h][k] = d < D ? pc[(int64_t)k * D + d] : 0.0f;
       }
-      __syncthreads();   // the previous chunk's (or tile's) list has been read
+      // the previous chunk's (or tile's) list has been read
+      if constexpr (EACH) {
+        const bool any = __ballot(dense) != 0;
+        if (lane == 0) s.each[wave] = any;
+      }
+      __syncthreads();
+      if constexpr (EACH)
+#pragma unroll
+        for (int w = 0; w < NW; ++w) dense |= s.each[w] != 0;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         bool nz = dense;
@@ -116,8 +147,10 @@ struct Tile {
           for (int k = 0; k < kK; ++k) s.p[e][k] = (double)v[h][k];
         }
       __syncthreads();
-      constexpr int kU = 4;   // rows of B in flight
-      for (int e0 = 0; e0 < n; e0 += kU) {
+      // rows of B in flight: 16 / CPT, and 4 for the last 4 and fewer (a block's
+      // few columns)
+      auto rows = [&](int e0, auto count) {
+        constexpr int kU = decltype(count)::value;
         float w[kU][CPT];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
@@ -134,13 +167,17 @@ struct Tile {
         for (int u = 0; u < kU; ++u)
           if (e0 + u < n) {
 #pragma unroll
-            for (int k = 0; k < kK; ++k) {
-              const double pv = s.p[e0 + u][k];
+            for (int k = 0; k < KPT; ++k) {
+              const double pv = s.p[e0 + u][kt + k];
 #pragma unroll
               for (int j = 0; j < CPT; ++j) t[k][j] = __fma_rn(pv, (double)w[u][j], t[k][j]);
             }
           }
-      }
+      };
+      int e0 = 0;
+      if constexpr (CPT < 4)
+        for (; n - e0 > 4; e0 += 16 / CPT) rows(e0, std::integral_constant<int, 16 / CPT>{});
+      for (; e0 < n; e0 += 4) rows(e0, std::integral_constant<int, 4>{});
     }
   }
 };
@@ -148,38 +185,21 @@ struct Tile {
 // a double at any byte address (the codes are a byte array)
 struct __attribute__((packed)) F64u { double v; };
 
-// The range of T over one (codebook, column tile), parked in the first 16
-// bytes of the tile's codes ([lo, hi]; a tile of any codebook has at least 16
-// bytes).  lo = NaN says that a weight among this workgroup's share of B is
-// not finite (a range of entries is never NaN: fmin and fmax skip NaN).
-template <int CPT, bool VEC>
-__global__ void __launch_bounds__(kBuildThreads)
-build_range_kernel(const float* __restrict__ P, const float* __restrict__ B, int C, int D, int M, int tiles,
-                   int8_t* lut) {
-  __shared__ TileLds s;
-  __shared__ double s_red[2][kBuildThreads / 64];
-  __shared__ int s_bad;
-  using T = Tile<CPT, VEC>;
-  const int c = blockIdx.x / tiles, tile = blockIdx.x % tiles;
-  const int col0 = tile * T::kCols;
-  if (threadIdx.x == 0) s_bad = 0;
-  double t[kK][CPT];
-  T::sums(P, B, D, M, c, col0, false, s, t);   // (has barriers: s_bad is set)
-  bool bad = false;
-  for (int d = (int)((int64_t)c * D / C); d < (int)((int64_t)(c + 1) * D / C); ++d)
+// lo and hi over this thread's entries of a tile
+template <class T>
+__device__ __forceinline__ void widen(const double (&t)[T::kKpt][T::kCpt], int col0, int M, double& lo, double& hi) {
 #pragma unroll
-    for (int j = 0; j < CPT; ++j)
-      bad |= !__builtin_isfinite(B[(int64_t)d * M + min(T::colof(col0, j), M - 1)]);
-  if (bad) s_bad = 1;
-  double lo = __builtin_inf(), hi = -__builtin_inf();
-#pragma unroll
-  for (int j = 0; j < CPT; ++j)
+  for (int j = 0; j < T::kCpt; ++j)
     if (T::colof(col0, j) < M)
 #pragma unroll
-      for (int k = 0; k < kK; ++k) {
+      for (int k = 0; k < T::kKpt; ++k) {
         lo = fmin(lo, t[k][j]);
         hi = fmax(hi, t[k][j]);
       }
+}
+
+// lo and hi over the workgroup, for thread 0 (true there); has a barrier
+__device__ __forceinline__ bool block_range(double (&s_red)[2][kBuildThreads / 64], double& lo, double& hi) {
   for (int o = 32; o > 0; o >>= 1) {
     lo = fmin(lo, __shfl_xor(lo, o));
     hi = fmax(hi, __shfl_xor(hi, o));
@@ -189,11 +209,34 @@ build_range_kernel(const float* __restrict__ P, const float* __restrict__ B, int
     s_red[1][threadIdx.x >> 6] = hi;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < kBuildThreads / 64; ++w) {
-      lo = fmin(lo, s_red[0][w]);
-      hi = fmax(hi, s_red[1][w]);
-    }
+  if (threadIdx.x != 0) return false;
+  for (int w = 1; w < kBuildThreads / 64; ++w) {
+    lo = fmin(lo, s_red[0][w]);
+    hi = fmax(hi, s_red[1][w]);
+  }
+  return true;
+}
+
+// The range of T over one (codebook, column tile), parked in the first 16
+// bytes of the tile's codes ([lo, hi]; a tile of any codebook has at least 16
+// bytes).  lo = NaN says that a weight among this workgroup's share of B is
+// not finite (a range of entries is never NaN: fmin and fmax skip NaN).
+template <class T>
+__global__ void __launch_bounds__(kBuildThreads)
+build_range_kernel(const float* __restrict__ P, const float* __restrict__ B, int C, int D, int M, int tiles,
+                   int8_t* lut) {
+  __shared__ TileLds s;
+  __shared__ double s_red[2][kBuildThreads / 64];
+  __shared__ int s_bad;
+  const int c = blockIdx.x / tiles, tile = blockIdx.x % tiles;
+  const int col0 = tile * T::kCols;
+  if (threadIdx.x == 0) s_bad = 0;
+  double t[T::kKpt][T::kCpt];
+  T::sums(P, B, D, M, c, col0, false, s, t);   // (has barriers: s_bad is set)
+  if (T::not_finite(B, (int64_t)c * D / C, (int64_t)(c + 1) * D / C, M, col0)) s_bad = 1;
+  double lo = __builtin_inf(), hi = -__builtin_inf();
+  widen<T>(t, col0, M, lo, hi);
+  if (block_range(s_red, lo, hi)) {
     F64u* out = reinterpret_cast<F64u*>(lut + (int64_t)c * kK * M + 16 * tile);
     out[0].v = s_bad ? __builtin_nan("") : lo;
     out[1].v = hi;
@@ -202,18 +245,29 @@ build_range_kernel(const float* __restrict__ P, const float* __restrict__ B, int
 
 constexpr int kDenseBit = 1 << 16;   // in a parked exponent: take every prototype column
 
-// Offset and exponent of codebook c = blockIdx.x from its tiles' ranges.
-// r = max |T - o| is taken at an end of the range (rounding is monotone).
-// With a non-finite weight anywhere the range is evaluated here over every
-// prototype column, and the codes are told to do the same.
-template <int CPT, bool VEC>
+// Offset and exponent of codebook c from its range; r = max |T - o| is taken at
+// an end of it (rounding is monotone).
+__device__ __forceinline__ void park_exponent(double lo, double hi, bool dense, int c, float* __restrict__ scale_out,
+                                              float* __restrict__ offset_out) {
+  const float o = (float)__ddiv_rn(__dadd_rn(lo, hi), 2.0);
+  const double r = fmax(fmax(0.0, fabs(__dsub_rn(lo, (double)o))), fabs(__dsub_rn(hi, (double)o)));
+  int ex = -126;
+  while (ex < 127 && r > 127.0 * __builtin_ldexp(1.0, ex)) ++ex;
+  offset_out[c] = o;
+  // parked, replaced by table_scale_kernel
+  reinterpret_cast<int*>(scale_out)[c] = ex + (dense ? kDenseBit : 0);
+}
+
+// The same from the ranges of its tiles, c = blockIdx.x.  With a non-finite
+// weight anywhere the range is evaluated here over every prototype column, and
+// the codes are told to do the same.
+template <class T>
 __global__ void __launch_bounds__(kBuildThreads)
 build_exponent_kernel(const float* __restrict__ P, const float* __restrict__ B, int C, int D, int M, int tiles,
                       const int8_t* lut, float* __restrict__ scale_out, float* __restrict__ offset_out) {
   __shared__ TileLds s;
   __shared__ double s_red[2][kBuildThreads / 64];
   __shared__ int s_bad;
-  using T = Tile<CPT, VEC>;
   const int c = blockIdx.x;
   if (threadIdx.x == 0) s_bad = 0;
   __syncthreads();
@@ -232,40 +286,29 @@ build_exponent_kernel(const float* __restrict__ P, const float* __restrict__ B, 
     }
   } else {
     for (int tile = 0; tile < tiles; ++tile) {
-      double t[kK][CPT];
+      double t[T::kKpt][T::kCpt];
       T::sums(P, B, D, M, c, tile * T::kCols, true, s, t);
-#pragma unroll
-      for (int j = 0; j < CPT; ++j)
-        if (T::colof(tile * T::kCols, j) < M)
-#pragma unroll
-          for (int k = 0; k < kK; ++k) {
-            lo = fmin(lo, t[k][j]);
-            hi = fmax(hi, t[k][j]);
-          }
+      widen<T>(t, tile * T::kCols, M, lo, hi);
     }
   }
-  for (int o = 32; o > 0; o >>= 1) {
-    lo = fmin(lo, __shfl_xor(lo, o));
-    hi = fmax(hi, __shfl_xor(hi, o));
-  }
-  if ((threadIdx.x & 63) == 0) {
-    s_red[0][threadIdx.x >> 6] = lo;
-    s_red[1][threadIdx.x >> 6] = hi;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < kBuildThreads / 64; ++w) {
-      lo = fmin(lo, s_red[0][w]);
-      hi = fmax(hi, s_red[1][w]);
-    }
-    const float o = (float)__ddiv_rn(__dadd_rn(lo, hi), 2.0);
-    const double r = fmax(fmax(0.0, fabs(__dsub_rn(lo, (double)o))), fabs(__dsub_rn(hi, (double)o)));
-    int ex = -126;
-    while (ex < 127 && r > 127.0 * __builtin_ldexp(1.0, ex)) ++ex;
-    offset_out[c] = o;
-    // parked, replaced by table_scale_kernel
-    reinterpret_cast<int*>(scale_out)[c] = ex + (dense ? kDenseBit : 0);
-  }
+  if (block_range(s_red, lo, hi)) park_exponent(lo, hi, dense, c, scale_out, offset_out);
+}
+
+// Both in one launch for tables of one tile and few weights: every workgroup
+// looks through all of B itself.
+template <class T>
+__global__ void __launch_bounds__(kBuildThreads)
+build_small_exponent_kernel(const float* __restrict__ P, const float* __restrict__ B, int D, int M,
+                            float* __restrict__ scale_out, float* __restrict__ offset_out) {
+  __shared__ TileLds s;
+  __shared__ double s_red[2][kBuildThreads / 64];
+  const int c = blockIdx.x;
+  const bool dense = D <= kAllColumns || __syncthreads_or(T::not_finite(B, 0, D, M, 0));
+  double t[T::kKpt][T::kCpt];
+  T::sums(P, B, D, M, c, 0, dense, s, t);
+  double lo = __builtin_inf(), hi = -__builtin_inf();
+  widen<T>(t, 0, M, lo, hi);
+  if (block_range(s_red, lo, hi)) park_exponent(lo, hi, dense, c, scale_out, offset_out);
 }
 
 __device__ __forceinline__ int parked_exponent(int v) { return v >= kDenseBit / 2 ? v - kDenseBit : v; }
@@ -276,34 +319,33 @@ __device__ __forceinline__ int8_t code_of(double t, double o, double inv) {
 
 __device__ int max_parked_exponent(const float* __restrict__ scale_out, int C, int* s_max);
 
-template <int CPT, bool VEC>
+template <class T>
 __global__ void __launch_bounds__(kBuildThreads)
 build_codes_kernel(const float* __restrict__ P, const float* __restrict__ B, int C, int D, int M, int tiles, int cap,
                    const float* __restrict__ scale_out, const float* __restrict__ offset_out,
                    int8_t* __restrict__ lut) {
   __shared__ TileLds s;
   __shared__ int s_max;
-  using T = Tile<CPT, VEC>;
   const int c = blockIdx.x / tiles, col0 = (blockIdx.x % tiles) * T::kCols;
   const int parked = reinterpret_cast<const int*>(scale_out)[c];
-  double t[kK][CPT];
+  double t[T::kKpt][T::kCpt];
   T::sums(P, B, D, M, c, col0, parked >= kDenseBit / 2, s, t);
   const int ex = max(parked_exponent(parked), max_parked_exponent(scale_out, C, &s_max) - cap);
   const double o = (double)offset_out[c], inv = __builtin_ldexp(1.0, -ex);
-  int8_t* out = lut + (int64_t)c * kK * M;
+  int8_t* out = lut + ((int64_t)c * kK + T::k0()) * M;
 #pragma unroll
-  for (int k = 0; k < kK; ++k) {
-    if constexpr (VEC) {   // M % 4 == 0: a thread's 4 columns exist together
+  for (int k = 0; k < T::kKpt; ++k) {
+    if constexpr (T::kVec) {   // M % 4 == 0: a thread's 4 columns exist together
       const int m = T::colof(col0, 0);
       if (m < M) {
         uint32_t q = 0;
 #pragma unroll
-        for (int j = 0; j < CPT; ++j) q |= (uint32_t)(uint8_t)code_of(t[k][j], o, inv) << (8 * j);
+        for (int j = 0; j < T::kCpt; ++j) q |= (uint32_t)(uint8_t)code_of(t[k][j], o, inv) << (8 * j);
         *reinterpret_cast<uint32_t*>(out + (int64_t)k * M + m) = q;
       }
     } else {
 #pragma unroll
-      for (int j = 0; j < CPT; ++j) {
+      for (int j = 0; j < T::kCpt; ++j) {
         const int m = T::colof(col0, j);
         if (m < M) out[(int64_t)k * M + m] = code_of(t[k][j], o, inv);
       }
@@ -311,26 +353,40 @@ build_codes_kernel(const float* __restrict__ P, const float* __restrict__ B, int
   }
 }
 
-template <int CPT, bool VEC>
+// The fp32 table.  A column that holds a weight that is not finite needs every
+// prototype column, and a workgroup with one takes them all.  Few weights
+// (SMALL) the workgroup looks through itself; else weights_kernel has, and
+// left word j of the 64 columns from 64 i, the bits of 32 of them, in the first
+// row of every codebook, at column 64 i + j.
+template <class T, bool SMALL>
 __global__ void __launch_bounds__(kBuildThreads)
-build_f32_kernel(const float* __restrict__ P, const float* __restrict__ B, int C, int D, int M, int tiles,
-                 float* __restrict__ lut) {
+build_f32_kernel(const float* __restrict__ P, const float* __restrict__ B, int C, int D, int M, int tiles, float* lut) {
   __shared__ TileLds s;
-  using T = Tile<CPT, VEC>;
   const int c = blockIdx.x / tiles, col0 = (blockIdx.x % tiles) * T::kCols;
-  double t[kK][CPT];
-  T::sums(P, B, D, M, c, col0, false, s, t);
-  float* out = lut + (int64_t)c * kK * M;
+  float* out = lut + ((int64_t)c * kK + T::k0()) * M;
+  bool bad = false;
+  if constexpr (SMALL) {
+    bad = D <= kAllColumns || T::not_finite(B, 0, D, M, col0);
+  } else {
+    const uint32_t* parked = reinterpret_cast<const uint32_t*>(lut + (int64_t)c * kK * M);
 #pragma unroll
-  for (int k = 0; k < kK; ++k) {
-    if constexpr (VEC) {
+    for (int j = 0; j < T::kCpt; ++j) {
+      const int m = min(T::colof(col0, j), M - 1);
+      bad |= (parked[(m & ~63) + (m >> 5 & 1)] >> (m & 31)) & 1;
+    }
+  }
+  double t[T::kKpt][T::kCpt];
+  T::template sums<true>(P, B, D, M, c, col0, bad, s, t);   // (every word has been read before any is replaced)
+#pragma unroll
+  for (int k = 0; k < T::kKpt; ++k) {
+    if constexpr (T::kVec) {
       const int m = T::colof(col0, 0);
       if (m < M)
         *reinterpret_cast<float4*>(out + (int64_t)k * M + m) =
             make_float4((float)t[k][0], (float)t[k][1], (float)t[k][2], (float)t[k][3]);
     } else {
 #pragma unroll
-      for (int j = 0; j < CPT; ++j) {
+      for (int j = 0; j < T::kCpt; ++j) {
         const int m = T::colof(col0, j);
         if (m < M) out[(int64_t)k * M + m] = (float)t[k][j];
       }
@@ -338,31 +394,39 @@ build_f32_kernel(const float* __restrict__ P, const float* __restrict__ B, int C
   }
 }
 
-// The fp32 table's entries of columns that hold a non-finite weight, over
-// every prototype column (the launch above skipped the zero ones): 64 columns
-// per workgroup, which reads them through once and is done if all are finite.
-constexpr int kRepairThreads = 1024;
-__global__ void __launch_bounds__(kRepairThreads)
-build_f32_repair_kernel(const float* __restrict__ P, const float* __restrict__ B, int C, int D, int M,
-                        float* __restrict__ lut) {
+// Small tables of few weights, an entry per thread and no list.
+__global__ void __launch_bounds__(kBuildThreads)
+build_f32_small_kernel(const float* __restrict__ P, const float* __restrict__ B, int D, int M, int total,
+                       float* __restrict__ lut) {
+  const int e = (int)blockIdx.x * kBuildThreads + (int)threadIdx.x;
+  if (e >= total) return;
+  const int row = e / M, m = e - row * M;
+  double t = 0.0;
+#pragma unroll 16
+  for (int d = 0; d < D; ++d) t = __fma_rn((double)P[row * D + d], (double)B[d * M + m], t);
+  lut[e] = (float)t;
+}
+
+// Which columns hold a weight that is not finite, 64 of them per workgroup.
+constexpr int kWeightThreads = 1024;
+__global__ void __launch_bounds__(kWeightThreads)
+weights_kernel(const float* __restrict__ B, int C, int D, int M, float* __restrict__ lut) {
   __shared__ int s_bad[64];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int m = blockIdx.x * 64 + lane;
+  const int m0 = blockIdx.x * 64, m = m0 + lane;
   if (tid < 64) s_bad[tid] = 0;
   __syncthreads();
   bool bad = false;
 #pragma unroll 8
-  for (int d = tid >> 6; d < D; d += kRepairThreads / 64)
+  for (int d = tid >> 6; d < D; d += kWeightThreads / 64)
     bad |= !__builtin_isfinite(B[(int64_t)d * M + min(m, M - 1)]);
-  if (bad && m < M) s_bad[lane] = 1;
+  if (bad) s_bad[lane] = 1;
   __syncthreads();
-  if (m >= M || !s_bad[lane]) return;
-  for (int row = tid >> 6; row < C * kK; row += kRepairThreads / 64) {
-    double t = 0.0;
-    for (int d = 0; d < D; ++d)
-      t = __fma_rn((double)P[(int64_t)row * D + d], (double)B[(int64_t)d * M + m], t);
-    lut[(int64_t)row * M + m] = (float)t;
-  }
+  const uint64_t mask = __ballot(s_bad[lane] != 0);   // (a column past M repeats M - 1; its bit is not read)
+  const int words = M - m0 > 32 ? 2 : 1;
+  for (int e = tid; e < C * words; e += kWeightThreads)
+    reinterpret_cast<uint32_t*>(lut)[(int64_t)(e / words) * kK * M + m0 + e % words] =
+        (uint32_t)(mask >> (32 * (e % words)));
 }
 
 // a given double table (a fitted one)
@@ -497,34 +561,57 @@ static hipError_t quantize(const Src& src, int C, int M, int8_t* lut, float* sca
   return hipGetLastError();
 }
 
-// Columns per thread of a tile: 4 (vector loads where the rows of B and of the
+// The tile.  4 columns per thread (vector loads where the rows of B and of the
 // codes are whole 16- and 4-byte units) when that leaves a workgroup for every
-// CU, else 1, so that small tables are spread over more of them.
+// CU, else 1, so that small tables are spread over more of them.  Narrow tables,
+// and fp32 ones of few codebooks, are spread over the prototypes too: with 16 of
+// them per thread most threads have none of up to 128 columns, and the others
+// 16 chains (prototypes without zero columns, 512 codebooks, 10 columns, 16 / 1
+// per thread: D 300 364 / 72 us with codes, 170 / 29 fp32; one codebook, D 1024,
+// 4096 columns fp32, 16 / 4 per thread, 236 / 94).
 template <class F>
-static hipError_t with_tile(const void* B, const void* lut, int lut_elem, int C, int M, int cus, F&& f) {
-  const int64_t wide = (int64_t)C * ((M + Tile<4, true>::kCols - 1) / Tile<4, true>::kCols);
-  if (wide < cus) return f(Tile<1, false>{}, (M + Tile<1, false>::kCols - 1) / Tile<1, false>::kCols);
+static hipError_t with_tile(const void* B, const void* lut, int lut_elem, int C, int D, int M, int cus, F&& f) {
+  if (M <= 16) return f(Tile<1, false, 1>{}, 1);
+  if (M <= 64) return f(Tile<1, false, 4>{}, 1);
+  if (M <= 128) return f(Tile<1, false, 8>{}, 1);
+  using Wide = Tile<4, true, kK>;
+  using One = Tile<1, false, kK>;
+  const int64_t wide = (int64_t)C * ((M + Wide::kCols - 1) / Wide::kCols);
+  if (wide < cus) {
+    const int ones = (M + One::kCols - 1) / One::kCols;
+    if (lut_elem == 4 && D > 16 && 2 * (int64_t)C * ones < cus)
+      return f(Tile<1, false, 4>{}, (M + 63) / 64);
+    return f(One{}, ones);
+  }
   const int tiles = (int)(wide / C);
   const bool vec = M % 4 == 0 && reinterpret_cast<uintptr_t>(B) % 16 == 0 &&
                    reinterpret_cast<uintptr_t>(lut) % (4 * lut_elem) == 0;
-  if (vec) return f(Tile<4, true>{}, tiles);
-  return f(Tile<4, false>{}, tiles);
+  if (vec) return f(Wide{}, tiles);
+  return f(Tile<4, false, kK>{}, tiles);
+}
+
+// Few weights: at most 16 per thread of a tile, which every workgroup looks
+// through in less than a launch takes.
+template <class T>
+static bool few_weights(int D) {
+  return (int64_t)D * T::kCols <= 16 * kBuildThreads;
 }
 
 hipError_t launch_build_lut(const float* P, const float* B, int C, int D, int M, int8_t* lut,
                             float* scale, float* offset, int cap, int cus, hipStream_t stream) {
-  hipError_t e = with_tile(B, lut, 1, C, M, cus, [&](auto tile, int tiles) {
-    constexpr int CPT = decltype(tile)::kCpt;
-    constexpr bool VEC = decltype(tile)::kVec;
+  hipError_t e = with_tile(B, lut, 1, C, D, M, cus, [&](auto tile, int tiles) {
+    using T = decltype(tile);
     const dim3 grid((unsigned)(C * tiles)), block(kBuildThreads);
-    hipLaunchKernelGGL((build_range_kernel<CPT, VEC>), grid, block, 0, stream, P, B, C, D, M, tiles, lut);
-    hipError_t r = hipGetLastError();
-    if (r != hipSuccess) return r;
-    hipLaunchKernelGGL((build_exponent_kernel<CPT, VEC>), dim3(C), block, 0, stream, P, B, C, D, M, tiles, lut, scale,
-                       offset);
+    hipError_t r;
+    if (tiles == 1 && few_weights<T>(D)) {
+      hipLaunchKernelGGL(build_small_exponent_kernel<T>, dim3(C), block, 0, stream, P, B, D, M, scale, offset);
+    } else {
+      hipLaunchKernelGGL(build_range_kernel<T>, grid, block, 0, stream, P, B, C, D, M, tiles, lut);
+      if ((r = hipGetLastError()) != hipSuccess) return r;
+      hipLaunchKernelGGL(build_exponent_kernel<T>, dim3(C), block, 0, stream, P, B, C, D, M, tiles, lut, scale, offset);
+    }
     if ((r = hipGetLastError()) != hipSuccess) return r;
-    hipLaunchKernelGGL((build_codes_kernel<CPT, VEC>), grid, block, 0, stream, P, B, C, D, M, tiles, cap, scale,
-                       offset, lut);
+    hipLaunchKernelGGL(build_codes_kernel<T>, grid, block, 0, stream, P, B, C, D, M, tiles, cap, scale, offset, lut);
     return hipGetLastError();
   });
   if (e != hipSuccess) return e;
@@ -540,15 +627,27 @@ hipError_t launch_quantize_lut(const double* T, int C, int M, int8_t* lut, float
 
 hipError_t launch_build_lut_f32(const float* P, const float* B, int C, int D, int M, float* lut, int cus,
                                 hipStream_t stream) {
-  hipError_t e = with_tile(B, lut, 4, C, M, cus, [&](auto tile, int tiles) {
-    hipLaunchKernelGGL((build_f32_kernel<decltype(tile)::kCpt, decltype(tile)::kVec>), dim3((unsigned)(C * tiles)),
-                       dim3(kBuildThreads), 0, stream, P, B, C, D, M, tiles, lut);
+  // Up to 16 columns of P and a few million products: an entry per thread (D 16,
+  // an entry per thread / in tiles: 16 x 256 3.7 / 6.5 us, 128 x 1000 13 / 7).
+  if (D <= 16 && (int64_t)C * kK * M * D <= 6000000) {
+    const int total = C * kK * M;
+    hipLaunchKernelGGL(build_f32_small_kernel, dim3(grid_for(total)), dim3(kBuildThreads), 0, stream, P, B, D, M, total,
+                       lut);
+    return hipGetLastError();
+  }
+  return with_tile(B, lut, 4, C, D, M, cus, [&](auto tile, int tiles) {
+    using T = decltype(tile);
+    const dim3 grid((unsigned)(C * tiles)), block(kBuildThreads);
+    if (few_weights<T>(D)) {
+      hipLaunchKernelGGL((build_f32_kernel<T, true>), grid, block, 0, stream, P, B, C, D, M, tiles, lut);
+      return hipGetLastError();
+    }
+    hipLaunchKernelGGL(weights_kernel, dim3((unsigned)((M + 63) / 64)), dim3(kWeightThreads), 0, stream, B, C, D, M, lut);
+    hipError_t r = hipGetLastError();
+    if (r != hipSuccess) return r;
+    hipLaunchKernelGGL((build_f32_kernel<T, false>), grid, block, 0, stream, P, B, C, D, M, tiles, lut);
     return hipGetLastError();
   });
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(build_f32_repair_kernel, dim3((unsigned)((M + 63) / 64)), dim3(kRepairThreads), 0, stream, P, B,
-                     C, D, M, lut);
-  return hipGetLastError();
 }
 
 }  // namespace mdn

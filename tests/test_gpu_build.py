@@ -1,8 +1,9 @@
 """Table build where its shortcuts begin and end: prototype columns that are
 all zero are skipped (none of them, most of them, whole codebooks, more columns
 than one list holds), weights and prototypes that are not finite, every tile
-form (4 columns per thread with 16-byte rows or without, 1 column), byte
-offsets of the codes.  Bit-exact against the oracle; where NaN or infinities
+form (4 columns per thread with 16-byte rows or without, 1 column, narrow tables
+spread over the prototypes), weights few enough for every workgroup to look
+through, byte offsets of the codes.  Bit-exact against the oracle; where NaN or infinities
 occur, against a double sum over every column and the quantizer of that table.
 """
 import ctypes
@@ -70,6 +71,10 @@ CASES = [  # C, D, M, kind, byte offset of the codes
     (90, 270, 3001, "scattered", 0),   # ragged last tile, M % 4 != 0
     (64, 1100, 4100, "scattered", 0),  # more columns than one list, ragged vector tile
     (512, 512, 17, "blocks", 0),
+    # narrow tables (16, 64, 128 columns), few weights and more than that
+    (3, 256, 16, "dense", 0), (3, 257, 16, "scattered", 2), (7, 64, 17, "dense", 0), (7, 65, 64, "blocks", 0),
+    (20, 600, 65, "dense", 1), (5, 32, 128, "dense", 0), (5, 33, 128, "blocks", 0), (2, 16, 129, "dense", 0),
+    (2, 17, 256, "dense", 0), (300, 16, 1000, "scattered", 0), (300, 3, 1024, "blocks", 0),
 ]
 
 
@@ -83,7 +88,8 @@ def test_build_matches_oracle(orc, C, D, M, kind, off):
     assert np.array_equal(host(mdn.build_lut_f32(dev(P), dev(B))), orc.build_lut_f32(P, B))
 
 
-@pytest.mark.parametrize("C,D,M", [(4, 64, 10), (66, 530, 4096)])
+@pytest.mark.parametrize("C,D,M", [(4, 64, 10), (66, 530, 4096), (4, 300, 16), (5, 70, 33), (5, 41, 100), (4, 6, 100),
+                                   (9, 41, 300), (260, 530, 1025), (3, 1030, 97)])
 @pytest.mark.parametrize("where", ["weight in a skipped column", "weight in a used column", "prototype"])
 def test_build_not_finite(C, D, M, where):
     P, B = problem(C, D, M, "blocks", seed=C)
