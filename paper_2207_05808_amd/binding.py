@@ -58,10 +58,13 @@ def _rows(A: torch.Tensor) -> Tuple[int, int, int]:
 def _native(A, split, thr, lut, scale, offset, col_bias, act, y_out, acc_out, idx_out, want_acc, want_idx):
     """The call marshalled natively, on the current stream: (y, acc, idx), or
     None when the arguments are not the plain valid case (the caller then goes
-    through its own checks, which raise) or the call reports an error."""
+    through its own checks, which raise), the call reports an error or there
+    is no native marshalling."""
     if type(A) is not torch.Tensor or not A.is_cuda or not (act is None or type(act) is int):
         return None
-    fused = _fused or _load_native()
+    fused = _fused if _fused is not None else _load_native()
+    if not fused:
+        return None
     return fused(A, split, thr, lut, scale, offset, col_bias, act, y_out, acc_out, idx_out, want_acc, want_idx,
                  torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
 
@@ -71,7 +74,8 @@ _fused = None
 
 def _load_native():
     global _fused
-    _fused = _lib.calls().fused
+    calls = _lib.calls()
+    _fused = calls.fused if calls else False
     return _fused
 
 

@@ -68,6 +68,10 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
         with ThreadPoolExecutor(max_workers=jobs) as ex:
             results = list(ex.map(_run, cmds))
         for (rc, errs), c in zip(results, cmds):
+            if rc != 0 and c is cmds[-1]:   # the library does without it (_lib.calls)
+                print(f"warning: {calls} not built, the compiler failed ({rc}) on {' '.join(c)}:\n{errs}",
+                      file=sys.stderr, flush=True)
+                continue
             if rc != 0:
                 raise RuntimeError(f"compiler failed ({rc}) on {' '.join(c)}:\n{errs}")
             if verbose and errs.strip():
@@ -79,7 +83,10 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
         if rc != 0:
             raise RuntimeError(f"link failed ({rc}):\n{errs}")
     os.replace(tmp, out)
-    os.replace(calls + ".tmp", calls)
+    if results[-1][0] == 0:
+        os.replace(calls + ".tmp", calls)
+    elif os.path.exists(calls):
+        os.remove(calls)   # (an older one may not fit the library or torch)
     return out
 
 

@@ -4,6 +4,7 @@ include/maddness.h declares, and rejects bad arguments before any HIP call
 import ctypes
 import os
 import re
+import warnings
 
 import pytest
 
@@ -144,6 +145,23 @@ def test_fused_two_phase_needs_index_array(L):
                                  NULL, NULL) == 1
     assert L.maddness_matmul_act_f32(FAKE, 4096, 256, 256, FAKE, FAKE, 256, FAKE, 1024, NULL, 3, FAKE,
                                      NULL, NULL) == 1
+
+
+def test_native_marshalling_missing(monkeypatch, tmp_path):
+    """Without _calls.so, or with one that does not load, there is one warning
+    and no native marshalling; the library itself is not touched."""
+    from paper_2207_05808_amd import _lib, binding
+    bad = tmp_path / "_calls.so"
+    bad.write_bytes(b"not a library")
+    for path in (str(tmp_path / "none.so"), str(bad)):
+        monkeypatch.setattr(_lib, "CALLS_PATH", path)
+        monkeypatch.setattr(_lib, "_calls", None)
+        monkeypatch.setattr(binding, "_fused", None)
+        with pytest.warns(UserWarning, match="is not used"):
+            assert not binding._load_native()
+        with warnings.catch_warnings():
+            warnings.simplefilter("error")
+            assert _lib.calls() is None and not binding._load_native()
 
 
 def test_library_imports_no_allocator():

@@ -115,3 +115,18 @@ def test_truth_values(call, yes, no):
     assert same(mdn.matmul(*t, *q, want_acc=no, want_idx=yes), (ref[0], None, ref[2]))
     assert same(mdn.matmul_f32(*t, k["tab"], want_idx=yes)[1], ref[2])
     assert mdn.matmul_f32(*t, k["tab"], want_idx=no)[1] is None
+
+
+def test_without_native_marshalling(call, monkeypatch, tmp_path):
+    """The binding serves every call itself where _calls.so is missing."""
+    from paper_2207_05808_amd import _lib
+    k = call
+    f = lambda: (mdn.matmul(k["A"], k["split"], k["thr"], k["lut"], k["scale"], k["offset"], want_acc=True, want_idx=True)
+                 + mdn.matmul_f32(k["A"], k["split"], k["thr"], k["tab"], want_idx=True))
+    ref = f()
+    monkeypatch.setattr(_lib, "CALLS_PATH", str(tmp_path / "none.so"))
+    monkeypatch.setattr(_lib, "_calls", None)
+    monkeypatch.setattr(binding, "_fused", None)
+    with pytest.warns(UserWarning, match="is not used"):
+        assert same(f(), ref)
+    assert same(f(), ref)
