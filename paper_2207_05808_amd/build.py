@@ -31,7 +31,10 @@ NOISE = "packed-fp32-ops"
 
 
 def _run(cmd):
-    r = subprocess.run(cmd, capture_output=True, text=True)
+    try:
+        r = subprocess.run(cmd, capture_output=True, text=True)
+    except OSError as e:   # no such compiler
+        return 127, str(e)
     errs = "\n".join(l for l in r.stderr.splitlines() if NOISE not in l)
     return r.returncode, errs
 

@@ -205,7 +205,9 @@ int plan(const Shape& s, Plan* out, bool single_tile_only) {
 // Gather-fused plan: C divides 64 and the whole table (plus one zero row,
 // staged as int16 for int8 tables) fits in LDS.  Returns false when the
 // shape does not qualify.  With `cus` = 0 (planning without a HIP call) the
-// split for many rows; it qualifies the same shapes.
+// split for many rows, which is the stricter check: few rows take fewer per
+// wavefront, with less LDS and smaller offsets, so a very large lda may qualify
+// with the CUs given only.
 bool plan_gfused(const Shape& s, GArgs* g, int* ng_out, int* uq_out, int* nw_out, int cus = 0) {
   if (s.C > 64 || (64 % s.C) != 0) return false;
   int nw = 16;   // one 1024-thread workgroup per CU stages the table once
@@ -1133,7 +1135,8 @@ int maddness_encoder_gram(const uint8_t* idx, int64_t N, int32_t C, int32_t* gra
 
 int64_t maddness_encoder_scatter_workspace_bytes(int64_t N, int32_t C) {
   if (N < 0 || N >= (1ll << 31) || C <= 0 || C > kMaxFitC) return -1;
-  return round_up64((int64_t)C * (N + 128) * 4, 256) + (int64_t)C * (kK + 1) * 4;   // row lists + 128 padding each
+  // row lists, 128 spare entries each (unused; the size callers have always been asked for), bucket starts
+  return round_up64((int64_t)C * (N + 128) * 4, 256) + (int64_t)C * (kK + 1) * 4;
 }
 
 int maddness_encoder_scatter(const uint8_t* idx, int64_t N, int32_t C, const float* Y, int32_t M, double* out,
@@ -1179,7 +1182,7 @@ int maddness_fit_lut_ridge(const uint8_t* idx, int64_t N, int32_t C, const float
 int64_t maddness_fit_lut_gd_workspace_bytes(int64_t N, int32_t C, int32_t M) {
   const int64_t ws = maddness_encoder_scatter_workspace_bytes(N, C);
   if (ws < 0 || M <= 0) return -1;
-  return 2 * round_up64(N * M * 8, 256) + round_up64((int64_t)C * kK * M * 8, 256) + ws;
+  return 2 * round_up64(N * M * 8, 256) + ws;
 }
 
 int maddness_fit_lut_gd(const uint8_t* idx, int64_t N, int32_t C, const float* Y, int32_t M, const float* col_bias,
@@ -1201,7 +1204,6 @@ int maddness_fit_lut_gd(const uint8_t* idx, int64_t N, int32_t C, const float* Y
   w += round_up64(N * M * 8, 256);
   double* D = reinterpret_cast<double*>(w);
   w += round_up64(N * M * 8, 256);
-  w += round_up64((int64_t)C * kK * M * 8, 256);   // (unused: the gradient is not stored)
   int32_t* perm = reinterpret_cast<int32_t*>(w);
   int32_t* start = reinterpret_cast<int32_t*>(w + round_up64((int64_t)C * (N + 128) * 4, 256));
   return status_from(launch_fit_gd(idx, N, C, Y, M, col_bias, act, T0, lambda, eta, iters, T_out, P, D, perm,

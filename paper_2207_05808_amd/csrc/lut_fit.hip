@@ -81,11 +81,7 @@ gram_kernel(const uint8_t* __restrict__ idx, int64_t N, int C, int nbc, int64_t 
 //
 // partition: one workgroup per codebook lists the rows bucket by bucket,
 // ascending within each bucket (a stable counting sort), perm[c][start_k ..] =
-// rows of bucket k, start[c][k] the bucket starts (start[c][16] = N).  Each
-// codebook's list is followed by 128 entries of row 0, read (and ignored) past the last
-// bucket.
-constexpr int kPermPad = 128;
-
+// rows of bucket k, start[c][k] the bucket starts (start[c][16] = N).
 constexpr int kPartWaves = 16;
 
 // One workgroup per codebook; wavefront w takes the w-th contiguous run of
@@ -159,8 +155,7 @@ partition_kernel(const uint8_t* __restrict__ idx, int64_t N, int C, int32_t* __r
   }
   if (threadIdx.x == 0) start[c * (kK + 1) + kK] = (int32_t)N;
   __syncthreads();
-  int32_t* pc = perm + (int64_t)c * (N + kPermPad);
-  if (threadIdx.x < kPermPad) pc[N + threadIdx.x] = 0;
+  int32_t* pc = perm + (int64_t)c * N;
   for (int64_t b = b0; b < b1; b += kU) {
     int key[kU];
     load(b, key);
@@ -187,16 +182,18 @@ partition_kernel(const uint8_t* __restrict__ idx, int64_t N, int C, int32_t* __r
 // (targets Y) or double (gradient residuals).  `done(bucket row, column, sum)`
 // takes the result: stores it, or takes the gradient step.
 //
-// The sum of a bucket is one chain of dependent adds (4.5 cycles each), and
-// buckets are uneven (the largest of a random tree's 16 holds about half of
-// the rows), so the adding wavefront does nothing else.  Bound: on small
-// layers that chain, on large ones the L2, which reads every row once per
+// The sum of a bucket is one chain of dependent adds, and buckets are uneven
+// (the largest of a random tree's 16 holds about half of the rows), so the adding
+// wavefront does nothing else.  Bound: on small layers that wavefront, at about 20
+// cycles a row with its LDS reads and its loop (of the 81 us below, 76 are left
+// without the loads from memory, 38 without the adds), on large ones the L2 as
+// well, which reads every row once per
 // codebook.  Column tiles go to XCDs (workgroup b runs on XCD b % 8): with a
 // number of tiles that divides 8, or a multiple of 8, each XCD reads its own
 // columns only, and TC is such that they fit its 4 MB L2 at the training sets'
 // sizes; else the tiles are taken one after the other.
 // Measured against one wavefront per codebook with its 16 buckets in turn:
-// 16,384 rows, 32 codebooks x 64 columns of doubles 554 -> 79 us (largest
+// 16,384 rows, 32 codebooks x 64 columns of doubles 554 -> 81 us (largest
 // bucket 9063 rows); 64 codebooks x 512 columns of floats 585 -> 163 us (2.1 GB
 // out of the L2s).
 constexpr int kScWaves = 8, kScPer = 8;   // wavefronts; rows of a loading lane per stage
@@ -263,7 +260,7 @@ __device__ __forceinline__ void scatter_bucket(const int32_t* __restrict__ perm,
     // valid, what is not used is ignored
     if (nst == 0) return;
     const V* yc = Y + min(m, M - 1);
-    const int32_t* pc = perm + (int64_t)c * (N + kPermPad);
+    const int32_t* pc = perm + (int64_t)c * N;
     const int64_t mine = p0 + lane / kPer % kDepth * kRows + (wave - 1) * kPer + lane % kPer;
     const int first = lane / TC * kScPer;   // this lane's first row of the wavefront's
     auto fetch = [&](int64_t st) { return pc[min(mine + st * kRows, p1 - 1)]; };
@@ -357,7 +354,7 @@ __device__ __forceinline__ void scatter_few_rows(const int32_t* __restrict__ per
   const int c = (int)(r / kK), k = (int)(r % kK);
   const int m = (int)(w % ntile) * 64 + lane;
   const V* yc = Y + min(m, M - 1);   // columns past M read column M - 1
-  const int32_t* pc = perm + (int64_t)c * (N + kPermPad);
+  const int32_t* pc = perm + (int64_t)c * N;
   const int64_t p0 = start[c * (kK + 1) + k], p1 = start[c * (kK + 1) + k + 1];
   double acc = 0.0;
   for (int64_t p = p0; p < p1; p += 64) {

@@ -256,7 +256,7 @@ __global__ void __launch_bounds__(kMWaves * 64) macc_kernel(const MArgs a) {
   if (a.bias_lds)   // zeros past the last column
     for (int m = tid; m < W; m += kMWaves * 64) s_bias[m] = col0 + m < M ? a.col_bias[col0 + m] : 0.0f;
 
-  // ---------------- the table slice into LDS, the next batch's loads behind it
+  // ---------------- the table slice into LDS, one batch of loads after the other
   {
     put_tab(0, d0);
 #pragma unroll 1
