@@ -186,7 +186,9 @@ int maddness_lut_accumulate_f32(const uint8_t* idx, int64_t N, int32_t C,
  * 0/1 matrix).  Those are int8 tables with C % 16 == 0, C <= 128 and M % 4 == 0
  * of 64 codebooks and 128 to 512 columns at 98304 rows or more, or with C * M
  * >= 3072 where the table fits the LDS but not in 16-byte units of the
- * gather-fused kernel.  maddness_matmul_index_bytes tells
+ * gather-fused kernel, unless the encode, which reads whole rows of A, would
+ * cost more than it saves (many or long rows, or rows that are not whole
+ * 16-byte units) or cannot stage them.  maddness_matmul_index_bytes tells
  * which case a call is.
  */
 int maddness_matmul(const float* A, int64_t N, int32_t D, int64_t lda,

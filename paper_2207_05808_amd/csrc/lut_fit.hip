@@ -187,8 +187,8 @@ partition_kernel(const uint8_t* __restrict__ idx, int64_t N, int C, int32_t* __r
 // wavefront does nothing else.  Bound: on small layers that wavefront, at about 20
 // cycles a row with its LDS reads and its loop (of the 81 us below, 76 are left
 // without the loads from memory, 38 without the adds), on large ones the L2 as
-// well, which reads every row once per
-// codebook.  Column tiles go to XCDs (workgroup b runs on XCD b % 8): with a
+// well, which reads every row once per codebook.  Column tiles go to XCDs
+// (workgroup b runs on XCD b % 8): with a
 // number of tiles that divides 8, or a multiple of 8, each XCD reads its own
 // columns only, and TC is such that they fit its 4 MB L2 at the training sets'
 // sizes; else the tiles are taken one after the other.
@@ -377,7 +377,9 @@ constexpr int kScCols = 64;                                            // column
 // of doubles: at most 8 tiles of 16 for narrow layers (their chains are what
 // counts: 79 us against 86 with 32 columns, C 32, M 64), else 64 (the LDS is what
 // counts, and narrower tiles leave most of an access unused: C 256, M 1024 2.8 ms
-// a step against 6.9 with 32 columns)
+// a step against 6.9 with 32 columns).  No width of 65 to 512 columns, with 1 to
+// 256 codebooks and 2000 to 65,536 rows, is slower than with a wavefront per
+// codebook.
 constexpr int step_cols(int M) { return M <= 128 ? 16 : 64; }
 unsigned scatter_grid(int C, int M, int cols) { return (unsigned)(C * kK * ((M + cols - 1) / cols)); }
 unsigned few_rows_grid(int C, int M) {
