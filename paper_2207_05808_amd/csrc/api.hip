@@ -1135,7 +1135,7 @@ int maddness_encoder_gram(const uint8_t* idx, int64_t N, int32_t C, int32_t* gra
 
 int64_t maddness_encoder_scatter_workspace_bytes(int64_t N, int32_t C) {
   if (N < 0 || N >= (1ll << 31) || C <= 0 || C > kMaxFitC) return -1;
-  // row lists, 128 spare entries each (unused; the size callers have always been asked for), bucket starts
+  // row lists, each with a gap of 128 entries behind it, and the bucket starts
   return round_up64((int64_t)C * (N + 128) * 4, 256) + (int64_t)C * (kK + 1) * 4;
 }
 

@@ -82,6 +82,12 @@ gram_kernel(const uint8_t* __restrict__ idx, int64_t N, int C, int nbc, int64_t 
 // partition: one workgroup per codebook lists the rows bucket by bucket,
 // ascending within each bucket (a stable counting sort), perm[c][start_k ..] =
 // rows of bucket k, start[c][k] the bucket starts (start[c][16] = N).
+// The lists lie N + 128 entries apart, so that a power of two of rows does not put
+// them at the same distance from each other's memory channels and cache sets (ten
+// gradient steps on 16,384 rows, 32 x 64: 1256 us, 1282 packed).  Nothing is kept
+// in the gaps.
+constexpr int kListGap = 128;
+
 constexpr int kPartWaves = 16;
 
 // One workgroup per codebook; wavefront w takes the w-th contiguous run of
@@ -155,7 +161,7 @@ partition_kernel(const uint8_t* __restrict__ idx, int64_t N, int C, int32_t* __r
   }
   if (threadIdx.x == 0) start[c * (kK + 1) + kK] = (int32_t)N;
   __syncthreads();
-  int32_t* pc = perm + (int64_t)c * N;
+  int32_t* pc = perm + (int64_t)c * (N + kListGap);
   for (int64_t b = b0; b < b1; b += kU) {
     int key[kU];
     load(b, key);
@@ -260,7 +266,7 @@ __device__ __forceinline__ void scatter_bucket(const int32_t* __restrict__ perm,
     // valid, what is not used is ignored
     if (nst == 0) return;
     const V* yc = Y + min(m, M - 1);
-    const int32_t* pc = perm + (int64_t)c * N;
+    const int32_t* pc = perm + (int64_t)c * (N + kListGap);
     const int64_t mine = p0 + lane / kPer % kDepth * kRows + (wave - 1) * kPer + lane % kPer;
     const int first = lane / TC * kScPer;   // this lane's first row of the wavefront's
     auto fetch = [&](int64_t st) { return pc[min(mine + st * kRows, p1 - 1)]; };
@@ -354,7 +360,7 @@ __device__ __forceinline__ void scatter_few_rows(const int32_t* __restrict__ per
   const int c = (int)(r / kK), k = (int)(r % kK);
   const int m = (int)(w % ntile) * 64 + lane;
   const V* yc = Y + min(m, M - 1);   // columns past M read column M - 1
-  const int32_t* pc = perm + (int64_t)c * N;
+  const int32_t* pc = perm + (int64_t)c * (N + kListGap);
   const int64_t p0 = start[c * (kK + 1) + k], p1 = start[c * (kK + 1) + k + 1];
   double acc = 0.0;
   for (int64_t p = p0; p < p1; p += 64) {
